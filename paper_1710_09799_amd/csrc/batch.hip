@@ -86,6 +86,7 @@ struct mln_batch {
   int64_t nt = 0, step = 0, nblocks = 0;
   int cur = 0;
   mln::DevBuf dinst, dtiles;
+  mln::FillPlan fill;  // the state at step 0 of all problems
   bool use_graph = true;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -283,8 +284,11 @@ int mln_init_batch(int32_t n_inst, const mln_medium *media, const mln_grid *grid
       return set_err(rc, m);
     }
     b->inst.push_back(h);
+    b->fill.add_plan(h->fill);
   }
-  int rc = configure(b.get(), variant, W, K);
+  int rc = b->fill.upload();
+  if (rc) return rc;
+  rc = configure(b.get(), variant, W, K);
   if (rc) return rc;
   *out = b.release();
   return MLN_OK;
@@ -314,12 +318,11 @@ int mln_batch_use_graph(mln_batch *b, int32_t on) {
 
 int mln_batch_reset(mln_batch *b) {
   if (!b) return set_err(MLN_EINVAL, "null batch");
-  for (mln_handle *h : b->inst) {
-    int rc = reset_state(h);
-    if (rc) return rc;
-  }
+  HIP_TRY(b->fill.run(b->stream));  // every problem's state in one launch
+  for (mln_handle *h : b->inst) reset_counters(h);
   b->step = 0;
   b->cur = 0;
+  HIP_TRY(hipStreamSynchronize(b->stream));
   return MLN_OK;
 }
 

@@ -9,40 +9,11 @@
 #include <vector>
 
 #include "../../include/mln.h"
+#include "fill.hpp"
 #include "fwd_kernels.hpp"
 #include "mln_internal.hpp"
 
 namespace mln {
-
-// Record a message for mln_last_error() and return `code`.
-int set_err(int code, const std::string &msg);
-
-#define HIP_TRY(expr)                                                                   \
-  do {                                                                                  \
-    hipError_t e_ = (expr);                                                             \
-    if (e_ != hipSuccess)                                                               \
-      return set_err(e_ == hipErrorOutOfMemory ? MLN_ENOMEM : MLN_EHIP,                 \
-                     std::string(#expr) + ": " + hipGetErrorString(e_));                \
-  } while (0)
-
-// A device allocation owned by the handle.
-struct DevBuf {
-  void *p = nullptr;
-  size_t bytes = 0;
-  ~DevBuf() {
-    if (p) (void)hipFree(p);
-  }
-  hipError_t alloc(size_t n) {
-    release();
-    bytes = n;
-    return hipMalloc(&p, n ? n : 1);
-  }
-  void release() {
-    if (p) (void)hipFree(p);
-    p = nullptr;
-    bytes = 0;
-  }
-};
 
 // Deep copy of an mln_medium (the handle keeps it for the adjoint's chain rule).
 struct MediumCopy {
@@ -72,6 +43,7 @@ struct MediumCopy {
 
 struct mln_handle {
   using DevBuf = mln::DevBuf;
+  using FillPlan = mln::FillPlan;
   mln::Factors f;
   mln::MediumCopy medium;
   mln_grid grid{};
@@ -102,8 +74,7 @@ struct mln_handle {
   int64_t nsnap = 0;
   DevBuf st_pop, st_e, st_probe;  // device staging for host outputs
   double *d_pop = nullptr, *d_e = nullptr, *d_probe = nullptr;
-  // initial state on the host
-  std::vector<unsigned char> z_init, e_init;
+  FillPlan fill;  // the state at step 0 (both ping-pong slots) and the probe's first sample
   // checkpoints of the forward run (for the adjoint)
   int64_t ckpt_every = 0, nckpt = 0, ckpt_count = 0;
   bool ckpt_ok = false;
@@ -159,6 +130,8 @@ namespace mln {
 
 // Restore the initial state (step 0) of the handle.  Synchronises the stream.
 int reset_state(mln_handle *h);
+// The host's part of it: step 0, slot 0, no checkpoints.
+void reset_counters(mln_handle *h);
 // After the last step: synchronise, copy host-side outputs back and check the
 // probe for non-finite values.
 int finish_run(mln_handle *h);

@@ -209,25 +209,25 @@ int upload_factors(mln_handle *h, FacDev<Real> &fd) {
   return mln::upload_factors<Real>(h->f, h->route, h->grid.dt, h->fac, h->pop, h->popc, fd);
 }
 
+// The plan of the state at step 0: one Bloch vector for every medium cell,
+// the source sample at cell 0, zero elsewhere (low parts after the high parts
+// with the compensated state or fields).
 template <typename Real>
-void build_init_state(mln_handle *h) {
-  const Factors &f = h->f;
-  const int D = f.D;
-  const std::vector<double> &s0 = (h->route == MLN_ROUTE_ROTATION) ? f.y0 : f.dprime0;
-  const int rows = h->comp ? 2 * D : D;
-  h->z_init.assign(sizeof(Real) * rows * h->ld, 0);
-  Real *zi = (Real *)h->z_init.data();
-  for (int j = 0; j < D; ++j)
-    for (int64_t c = 0; c < h->nmed; ++c) {
-      zi[j * h->ld + c] = (Real)s0[j];
-      if (h->comp) zi[(D + j) * h->ld + c] = (Real)(s0[j] - (double)(Real)s0[j]);
-    }
-  // E (and with the compensated state its low parts after nx high parts)
-  const int64_t nx = h->grid.nx;
-  h->e_init.assign(sizeof(Real) * (h->cf ? 2 : 1) * nx, 0);
-  const double e0 = h->amp * h->samples[0];
-  ((Real *)h->e_init.data())[0] = (Real)e0;
-  if (h->cf) ((Real *)h->e_init.data())[nx] = (Real)(e0 - (double)(Real)e0);
+int build_init_state(mln_handle *h) {
+  std::vector<double> z0 = (h->route == MLN_ROUTE_ROTATION) ? h->f.y0 : h->f.dprime0;
+  std::vector<double> e0 = {h->amp * h->samples[0]};
+  if (h->comp)
+    for (int j = 0; j < h->f.D; ++j) z0.push_back(z0[j] - (double)(Real)z0[j]);
+  if (h->cf) e0.push_back(e0[0] - (double)(Real)e0[0]);
+  const int64_t nx = h->grid.nx, fields = h->cf ? 2 : 1;
+  const int rs = (int)sizeof(Real);
+  for (int b = 0; b < 2; ++b) {
+    h->fill.add(h->E[b].p, fields, nx, 1, e0, rs);
+    h->fill.add(h->H[b].p, fields, nx, 0, {}, rs);
+    h->fill.add(h->z[b].p, (int64_t)z0.size(), h->ld, h->nmed, z0, rs);
+  }
+  h->fill.add(h->d_probe, 1, 1, 0, {}, 8);  // E at cell nx - 1 >= 2
+  return h->fill.upload();
 }
 
 size_t state_slot_bytes(const mln_handle *h) { return h->E[0].bytes + h->H[0].bytes + h->z[0].bytes; }
@@ -467,27 +467,22 @@ int init_typed(mln_handle *h, FacDev<Real> &fd) {
     HIP_TRY(h->H[b].alloc((h->cf ? 2 : 1) * nx * sizeof(Real)));
     HIP_TRY(h->z[b].alloc((size_t)(h->comp ? 2 * D : D) * h->ld * sizeof(Real)));
   }
-  build_init_state<Real>(h);
-  return MLN_OK;
+  return build_init_state<Real>(h);
 }
 
 }  // namespace
 
-int mln::reset_state(mln_handle *h) {
-  for (int b = 0; b < 2; ++b) {
-    HIP_TRY(hipMemsetAsync(h->H[b].p, 0, h->H[b].bytes, h->stream));
-    HIP_TRY(hipMemcpyAsync(h->E[b].p, h->e_init.data(), h->e_init.size(), hipMemcpyHostToDevice, h->stream));
-    HIP_TRY(hipMemcpyAsync(h->z[b].p, h->z_init.data(), h->z_init.size(), hipMemcpyHostToDevice, h->stream));
-  }
+void mln::reset_counters(mln_handle *h) {
   h->cur = 0;
   h->step = 0;
   h->ckpt_count = 0;
   h->ckpt_ok = h->ckpt_every > 0;
   h->tape_ok = h->tape_all;
-  if (h->d_probe) {
-    double p0 = (h->grid.nx - 1 == 0) ? h->amp * h->samples[0] : 0.0;
-    HIP_TRY(hipMemcpyAsync(h->d_probe, &p0, sizeof(double), hipMemcpyHostToDevice, h->stream));
-  }
+}
+
+int mln::reset_state(mln_handle *h) {
+  HIP_TRY(h->fill.run(h->stream));
+  reset_counters(h);
   HIP_TRY(hipStreamSynchronize(h->stream));
   return MLN_OK;
 }

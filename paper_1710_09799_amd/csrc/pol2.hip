@@ -30,6 +30,7 @@ struct mln_pol2 {
   std::vector<double> u0, src_host;
   DevBuf fac, src, u[2], Ez[2], Hy[2], Ey[2], G[2];
   int cur = 0;
+  FillPlan fill;  // the state at step 0
 };
 
 namespace {
@@ -161,26 +162,26 @@ std::vector<double> pol2_factors(const Factors &fz, const Factors &fy, double dt
 }
 
 int pol2_reset(mln_pol2 *p) {
-  const int64_t nx = p->grid.nx;
-  std::vector<double> ez(nx, 0.0), ey(nx, 0.0);
-  ez[0] = p->amp_z * p->src_host[0];
-  ey[0] = p->amp_y * p->src_host[0];
-  for (int b = 0; b < 2; ++b) {
-    HIP_TRY(hipMemcpy(p->Ez[b].p, ez.data(), nx * sizeof(double), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(p->Ey[b].p, ey.data(), nx * sizeof(double), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemset(p->Hy[b].p, 0, p->Hy[b].bytes));
-    HIP_TRY(hipMemset(p->G[b].p, 0, p->G[b].bytes));
-  }
-  std::vector<double> ub((size_t)p->D * p->ld, 0.0);
-  for (int j = 0; j < p->D; ++j)
-    for (int64_t c = 0; c < p->nmed; ++c) ub[(size_t)j * p->ld + c] = p->u0[j];
-  HIP_TRY(hipMemcpy(p->u[0].p, ub.data(), ub.size() * sizeof(double), hipMemcpyHostToDevice));
-  const double zero = 0.0;  // E at cell nx - 1 before the first step
-  if (p->rec.probe_z_out) HIP_TRY(hipMemcpy(p->rec.probe_z_out, &zero, sizeof(double), hipMemcpyHostToDevice));
-  if (p->rec.probe_y_out) HIP_TRY(hipMemcpy(p->rec.probe_y_out, &zero, sizeof(double), hipMemcpyHostToDevice));
+  HIP_TRY(p->fill.run(p->stream));
   p->cur = 0;
   p->step = 0;
+  HIP_TRY(hipStreamSynchronize(p->stream));
   return MLN_OK;
+}
+
+// The plan of the state at step 0 (the probes: E at cell nx - 1 >= 2).
+int pol2_plan(mln_pol2 *p) {
+  const int64_t nx = p->grid.nx;
+  for (int b = 0; b < 2; ++b) {
+    p->fill.add(p->Ez[b].p, 1, nx, 1, {p->amp_z * p->src_host[0]}, 8);
+    p->fill.add(p->Ey[b].p, 1, nx, 1, {p->amp_y * p->src_host[0]}, 8);
+    p->fill.add(p->Hy[b].p, 1, nx - 1, 0, {}, 8);
+    p->fill.add(p->G[b].p, 1, nx - 1, 0, {}, 8);
+  }
+  p->fill.add(p->u[0].p, p->D, p->ld, p->nmed, p->u0, 8);
+  p->fill.add(p->rec.probe_z_out, 1, 1, 0, {}, 8);
+  p->fill.add(p->rec.probe_y_out, 1, 1, 0, {}, 8);
+  return p->fill.upload();
 }
 
 int pol2_steps(mln_pol2 *p, int64_t n) {
@@ -320,6 +321,8 @@ int mln_pol2_init(const mln_medium *medium, const double *dipole_y, const mln_gr
     HIP_TRY(p->G[b].alloc((g.nx - 1) * sizeof(double)));
   }
   for (int b = 0; b < 2; ++b) HIP_TRY(p->u[b].alloc((size_t)p->D * p->ld * sizeof(double)));
+  rc = pol2_plan(p.get());
+  if (rc) return rc;
   rc = pol2_reset(p.get());
   if (rc) return rc;
   *out = p.release();
@@ -356,7 +359,6 @@ int mln_pol2_run(mln_pol2 *p) {
 
 int mln_pol2_reset(mln_pol2 *p) {
   if (!p) return set_err(MLN_EINVAL, "null handle");
-  HIP_TRY(hipStreamSynchronize(p->stream));
   return pol2_reset(p);
 }
 

@@ -103,23 +103,16 @@ struct mln_pstd {
   double ca = 0, cb = 0, ah = 0, be = 0;
   std::vector<std::unique_ptr<Inst>> inst;
   DevBuf E, H, z, tab, dinst;
-  std::vector<double> e_init, h_init, z_init;
+  DevBuf E0, H0;  // the initial fields
+  FillPlan fill;  // the media's state at step 0 and the probes' first samples
 };
 
 namespace {
 
 int pstd_reset(mln_pstd *p) {
-  const int64_t nx = p->grid.nx;
-  HIP_TRY(hipMemcpyAsync(p->E.p, p->e_init.data(), p->e_init.size() * sizeof(double), hipMemcpyHostToDevice,
-                         p->stream));
-  HIP_TRY(hipMemcpyAsync(p->H.p, p->h_init.data(), p->h_init.size() * sizeof(double), hipMemcpyHostToDevice,
-                         p->stream));
-  HIP_TRY(hipMemcpyAsync(p->z.p, p->z_init.data(), p->z_init.size() * sizeof(double), hipMemcpyHostToDevice,
-                         p->stream));
-  for (int i = 0; i < p->n_inst; ++i)
-    if (p->inst[i]->d_probe)
-      HIP_TRY(hipMemcpyAsync(p->inst[i]->d_probe, &p->e_init[(size_t)i * nx + nx - 1], sizeof(double),
-                             hipMemcpyHostToDevice, p->stream));
+  HIP_TRY(hipMemcpyAsync(p->E.p, p->E0.p, p->E.bytes, hipMemcpyDeviceToDevice, p->stream));
+  HIP_TRY(hipMemcpyAsync(p->H.p, p->H0.p, p->H.bytes, hipMemcpyDeviceToDevice, p->stream));
+  HIP_TRY(p->fill.run(p->stream));
   HIP_TRY(hipStreamSynchronize(p->stream));
   p->step = 0;
   return MLN_OK;
@@ -264,11 +257,12 @@ int mln_pstd_init(int32_t n_inst, const mln_medium *media, const mln_grid *grid,
   p->ah = (g.dt / mu) * k0;
   p->be = (p->cb / (double)M) * k0;
   const int D = N * N - 1;
-  p->e_init.assign((size_t)n_inst * nx, 0.0);
-  p->h_init.assign((size_t)n_inst * nx, 0.0);
-  if (e_init) std::copy(e_init, e_init + (size_t)n_inst * nx, p->e_init.begin());
-  if (h_init) std::copy(h_init, h_init + (size_t)n_inst * nx, p->h_init.begin());
-  p->z_init.assign((size_t)n_inst * D * p->ld, 0.0);
+  for (auto f : {std::make_pair(&p->E0, e_init), std::make_pair(&p->H0, h_init)}) {
+    const size_t bytes = (size_t)n_inst * nx * sizeof(double);
+    HIP_TRY(f.first->alloc(bytes));
+    const std::vector<double> zero(f.second ? 0 : (size_t)n_inst * nx, 0.0);
+    HIP_TRY(hipMemcpy(f.first->p, f.second ? f.second : zero.data(), bytes, hipMemcpyHostToDevice));
+  }
   HIP_TRY(p->E.alloc((size_t)n_inst * nx * sizeof(double)));
   HIP_TRY(p->H.alloc((size_t)n_inst * nx * sizeof(double)));
   HIP_TRY(p->z.alloc((size_t)n_inst * D * p->ld * sizeof(double)));
@@ -280,8 +274,6 @@ int mln_pstd_init(int32_t n_inst, const mln_medium *media, const mln_grid *grid,
     if (rc) return set_err(rc, ctx(i) + err);
     rc = upload_factors<double>(I->f, MLN_ROUTE_ROTATION, g.dt, I->fac, I->pop, I->popc, I->fd);
     if (rc) return rc;
-    for (int j = 0; j < D; ++j)
-      for (int64_t c = 0; c < p->nmed; ++c) p->z_init[((size_t)i * D + j) * p->ld + c] = I->f.y0[j];
     I->rec = records ? records[i] : mln_record{};
     const mln_record &r = I->rec;
     if (r.out_on_device) {
@@ -314,6 +306,8 @@ int mln_pstd_init(int32_t n_inst, const mln_medium *media, const mln_grid *grid,
     d.probe = I->d_probe;
     d.e_out = I->d_e;
     d.pop_out = I->d_pop;
+    p->fill.add(d.z, D, p->ld, p->nmed, I->f.y0, 8);
+    p->fill.add_dev(d.probe, 1, 1, 1, (const double *)p->E0.p + (size_t)i * nx + nx - 1, 8);
     p->inst.push_back(std::move(I));
   }
   HIP_TRY(p->dinst.alloc(hi.size() * sizeof(PstdInst)));
@@ -343,7 +337,9 @@ int mln_pstd_init(int32_t n_inst, const mln_medium *media, const mln_grid *grid,
   }
   HIP_TRY(p->tab.alloc(tab.size() * sizeof(double2)));
   HIP_TRY(hipMemcpy(p->tab.p, tab.data(), tab.size() * sizeof(double2), hipMemcpyHostToDevice));
-  int rc = pstd_reset(p.get());
+  int rc = p->fill.upload();
+  if (rc) return rc;
+  rc = pstd_reset(p.get());
   if (rc) return rc;
   *out = p.release();
   return MLN_OK;
