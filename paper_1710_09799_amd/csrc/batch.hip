@@ -19,24 +19,34 @@ namespace mln {
 template <typename Real, bool COMP, bool CF>
 void launch_block_batch(bool many, dim3 grid, dim3 block, const BatchInst<Real> *inst, const BatchTile *tiles,
                         int64_t step0, int nsteps, int slot, hipStream_t st) {
-  if (many)
-    hipLaunchKernelGGL((fwd_block_batch_kernel<Real, COMP, CF>), grid, block, 0, st, inst, tiles, step0, nsteps,
-                       slot);
-  else
+  if (!many) {
     hipLaunchKernelGGL((fwd_block_batch_kernel_few<Real, COMP, CF>), grid, block, 0, st, inst, tiles, step0,
                        nsteps, slot);
+  } else if constexpr (CF) {
+    hipLaunchKernelGGL((fwd_block_batch_kernel<Real, COMP, CF>), grid, block, 0, st, inst, tiles, step0, nsteps,
+                       slot);
+  } else {  // one wavefront per tile
+    const dim3 wave(64);
+    switch (block.x / 64) {
+      case 1: hipLaunchKernelGGL((fwd_lane_batch_kernel<Real, COMP, 1>), grid, wave, 0, st, inst, tiles, step0, nsteps, slot); break;
+      case 2: hipLaunchKernelGGL((fwd_lane_batch_kernel<Real, COMP, 2>), grid, wave, 0, st, inst, tiles, step0, nsteps, slot); break;
+      case 3: hipLaunchKernelGGL((fwd_lane_batch_kernel<Real, COMP, 3>), grid, wave, 0, st, inst, tiles, step0, nsteps, slot); break;
+      default: hipLaunchKernelGGL((fwd_lane_batch_kernel<Real, COMP, 4>), grid, wave, 0, st, inst, tiles, step0, nsteps, slot); break;
+    }
+  }
 }
 
 // quad = true: four lanes per cell (4 W threads per workgroup); false: one
-// cell per thread (W threads), compiled for seven wavefronts per SIMD when
-// the launch has many tiles (many_tiles).
+// cell per thread (W threads), or one wavefront per tile (lane_better; with
+// float-float fields the build for seven wavefronts per SIMD, many_tiles).
 template <typename Real>
 hipError_t launch_fwd_batch(bool quad, bool comp, bool cf, int W, const BatchInst<Real> *inst,
                             const BatchTile *tiles, int64_t nblocks, int64_t step0, int nsteps, int slot,
                             hipStream_t st) {
   if (nblocks <= 0) return hipSuccess;
   const dim3 grid((unsigned)nblocks), block(quad ? 4 * W : W);
-  const bool many = many_tiles(nblocks);
+  // one wavefront per tile (plain fields), or the small register budget (float-float fields)
+  const bool many = cf ? many_tiles(nblocks) : lane_better(W, nblocks, device_cus());
   if (cf && !comp) {
     // plain single-precision state, float-float fields
     if constexpr (std::is_same<Real, float>::value) {
@@ -131,8 +141,12 @@ int upload_tables(mln_batch *b) {
     }
     h->cur = keep;
     hi[i].n_levels = h->f.N;
-    for (int64_t t = 0; t < h->ntiles; ++t) tiles.push_back(BatchTile{(int32_t)i, (int32_t)t});
   }
+  // the longer tiles first: the two-level ones fill the last round
+  for (int n : {3, 2})
+    for (size_t i = 0; i < b->inst.size(); ++i)
+      for (int64_t t = 0; b->inst[i]->f.N == n && t < b->inst[i]->ntiles; ++t)
+        tiles.push_back(BatchTile{(int32_t)i, (int32_t)t});
   HIP_TRY(hipStreamSynchronize(b->stream));
   HIP_TRY(b->dinst.alloc(hi.size() * sizeof(BatchInst<Real>)));
   HIP_TRY(hipMemcpy(b->dinst.p, hi.data(), hi.size() * sizeof(BatchInst<Real>), hipMemcpyHostToDevice));
@@ -255,8 +269,23 @@ int mln_init_batch(int32_t n_inst, const mln_medium *media, const mln_grid *grid
     return set_err(MLN_ENOTSUPPORTED, "batched launch: one-cell-per-thread or four-lanes-per-cell tiles");
   if (opt.ckpt_every != 0) return set_err(MLN_ENOTSUPPORTED, "batched launch: no checkpoints");
   const int variant = opt.variant == 0 ? 1 : opt.variant;
-  const int W = opt.tile > 0 ? opt.tile : (variant == 3 ? 128 : 256);
-  const int K = opt.steps_per_launch > 0 ? opt.steps_per_launch : 16;
+  int W = opt.tile > 0 ? opt.tile : (variant == 3 ? 128 : 256);
+  int K = opt.steps_per_launch > 0 ? opt.steps_per_launch : 16;
+  const bool fields = opt.precision == MLN_FP32_COMP_FIELDS || opt.precision == MLN_FP32_FIELDS;
+  if (variant == 1 && !fields && opt.tile <= 0 && opt.steps_per_launch <= 0) {
+    // one-wavefront tiles: the plan of one grid of all problems' cells
+    int64_t cells = 0;
+    int N = 2;
+    for (int32_t i = 0; i < n_inst; ++i) {
+      cells += std::max<int64_t>(0, grids[i].nx);
+      N = std::max(N, (int)media[i].n_levels);
+    }
+    const bool comp = opt.precision == MLN_FP32_COMP;
+    const int rs = opt.precision == MLN_FP64 ? 8 : 4;
+    const LanePlan p = lane_plan(N, opt.precision == MLN_FP32, rs * (2 + (N * N - 1) * (comp ? 2 : 1)), cells, device_cus());
+    W = p.W;
+    K = p.K;
+  }
   if (!valid_tiling(variant, W, K))
     return set_err(MLN_EINVAL, "batch tiling: variant 3 (tile a multiple of 16 in [32, 256]) or 1 (a multiple "
                                "of 64 in [64, 256]), 2 steps_per_launch < tile, steps_per_launch <= 128");
@@ -364,7 +393,8 @@ int mln_batch_tune(mln_batch *b, int32_t trial_steps, int32_t *variant, int32_t 
   static const int cand[][3] = {{3, 64, 8},   {3, 64, 16},  {3, 96, 16},  {3, 128, 8},  {3, 128, 16},
                                 {3, 128, 32}, {3, 192, 16}, {3, 192, 32}, {3, 256, 16}, {3, 256, 32},
                                 {3, 256, 64}, {1, 128, 16}, {1, 128, 32}, {1, 192, 16}, {1, 192, 32},
-                                {1, 256, 16}, {1, 256, 32}, {1, 256, 64}};
+                                {1, 256, 16}, {1, 256, 32}, {1, 256, 64}, {1, 64, 8},   {1, 64, 16},
+                                {1, 128, 8},  {1, 128, 12}, {1, 128, 24}, {1, 256, 20}, {1, 256, 24}};
   hipEvent_t e0, e1;
   HIP_TRY(hipEventCreate(&e0));
   HIP_TRY(hipEventCreate(&e1));

@@ -11,6 +11,7 @@
 // a whole run is fixed and can be captured in a HIP graph.
 #pragma once
 
+#include "fwd_lane.hpp"
 #include "fwd_quad.hpp"
 
 namespace mln {
@@ -44,15 +45,14 @@ __global__ void __launch_bounds__(1024)
     quad_tile<3, Real, COMP, CF>(a, bt.tile);
 }
 
-// Compiled for seven wavefronts per SIMD: the default register budget held
-// 3-4 (115 to 135 VGPRs) and left the vector units half idle.  Measured on
-// the 64-problem sweep (tile 256, 16 steps per launch), cell-updates/s
-// against the default budget: FP64 1.04e11 / 8.78e10, FP32 1.64e11 /
-// 1.50e11, compensated state 9.27e10 / 8.58e10, compensated state and
-// fields 8.50e10 / 6.61e10, compensated fields 1.46e11 / 1.29e11; five, six
-// and eight wavefronts were slower than seven.  The budget costs spills
-// (12-156 B per lane, some inside the step loop); the added wavefronts
-// more than pay for them when there are many tiles (many_tiles).
+// Float-float fields, compiled for seven wavefronts per SIMD: the default
+// register budget held 3-4 (115 to 135 VGPRs) and left the vector units half
+// idle.  Measured on the 64-problem sweep (tile 256, 16 steps per launch),
+// cell-updates/s against the default budget: compensated state and fields
+// 8.50e10 / 6.61e10, compensated fields 1.46e11 / 1.29e11; five, six and eight
+// wavefronts were slower than seven.  The budget costs spills (12-156 B per
+// lane, some inside the step loop); the added wavefronts more than pay for
+// them when there are many tiles (many_tiles).
 template <typename Real, bool COMP, bool CF>
 __device__ __forceinline__ void block_batch_tile(const BatchInst<Real> *__restrict__ inst,
                                                  const BatchTile *__restrict__ tiles, int64_t step0, int nsteps,
@@ -70,6 +70,31 @@ __global__ void __launch_bounds__(kMaxTile) __attribute__((amdgpu_waves_per_eu(7
     fwd_block_batch_kernel(const BatchInst<Real> *__restrict__ inst, const BatchTile *__restrict__ tiles,
                            int64_t step0, int nsteps, int slot) {
   block_batch_tile<Real, COMP, CF>(inst, tiles, step0, nsteps, slot);
+}
+// One wavefront per tile of 64 C cells (fwd_lane.hpp), plain and compensated
+// state.  The 64-problem sweep, tile 256 and 16 steps per launch,
+// cell-updates/s against one cell per thread in its build for seven
+// wavefronts per SIMD: FP64 1.39e11 / 1.01e11, compensated state 1.35e11 /
+// 9.24e10, FP32 1.77e11 / 1.62e11.
+template <typename Real, bool COMP, int C>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(lane_waves<3, Real, COMP, C>(), 8)))
+fwd_lane_batch_kernel(const BatchInst<Real> *__restrict__ inst, const BatchTile *__restrict__ tiles, int64_t step0,
+                      int nsteps, int slot) {
+  const BatchTile bt = tiles[blockIdx.x];
+  const BatchInst<Real> &bi = inst[bt.inst];
+  const FwdArgs<Real> a = bi.a[slot];
+  const ColdArgs<Real> cold = (ColdArgs<Real>)&bi.a[slot];
+  int s_snap = -1;  // first step n >= step0 with (n+1) % snap_every == 0
+  int64_t si = 0;
+  if (a.snap_every > 0) {
+    si = step0 / a.snap_every;
+    const int64_t n = (si + 1) * a.snap_every - 1;
+    if (n < step0 + nsteps) s_snap = (int)(n - step0);
+  }
+  if (bi.n_levels == 2)
+    lane_tile<2, Real, COMP, C>(a, cold, bt.tile, step0, nsteps, s_snap, si);
+  else
+    lane_tile<3, Real, COMP, C>(a, cold, bt.tile, step0, nsteps, s_snap, si);
 }
 // the default register budget, for batches of few tiles
 template <typename Real, bool COMP, bool CF>

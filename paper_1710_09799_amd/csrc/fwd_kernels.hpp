@@ -3,7 +3,10 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
+
+#include "lane_plan.hpp"
 
 namespace mln {
 
@@ -19,22 +22,27 @@ constexpr int kStreamCells = 1;           // consecutive cells per thread of the
 constexpr int kPadeMax = 7;              // highest Pade degree of the per-step Pade route
 constexpr size_t kPadeMaxLds = 160 * 1024;  // LDS of one compute unit
 
-// Launches of the one-cell-per-thread tile kernels with at least four tiles
-// per compute unit fill the default register budget's occupancy (three to
-// five 256-thread workgroups per unit), so they take the builds compiled for
-// seven wavefronts per SIMD; launches with fewer tiles keep the default
-// build, whose step does not pay for the spills of the smaller budget.
-inline bool many_tiles(int64_t nblocks) {
-  static int cache[64] = {0};
+// Compute units of the current device (256 where they cannot be asked for).
+inline int device_cus() {
+  static std::atomic<int> cache[64];
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
-  if (!cache[dev]) {
-    int cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+  int cus = cache[dev].load(std::memory_order_relaxed);
+  if (!cus) {
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
-    cache[dev] = cus;
+    cache[dev].store(cus, std::memory_order_relaxed);
   }
-  return nblocks >= 4 * (int64_t)cache[dev];
+  return cus;
 }
+
+// Launches of the one-cell-per-thread tile kernels with float-float fields
+// and at least four tiles per compute unit fill the default register budget's
+// occupancy (three to five 256-thread workgroups per unit), so they take the
+// builds compiled for seven wavefronts per SIMD; launches with fewer tiles
+// keep the default build, whose step does not pay for the spills of the
+// smaller budget.  (With plain fields the one-wavefront kernel takes such
+// launches.)
+inline bool many_tiles(int64_t nblocks) { return nblocks >= 4 * (int64_t)device_cus(); }
 
 // Device copies of the per-medium factors, in the precision of the state.
 // Indices are uniform across a wavefront, so the compiler reads them with
@@ -57,6 +65,7 @@ struct FacDev {
   const Real *Up;     // kPadeMax x D x D  per-step Pade route: V^k, k = 1..kPadeMax, V = dt U / unorm
   Real unorm;         // ||dt U||_1 (X = E dt U = (E unorm) V)
   Real p0;
+  const double *blk64; // compensated FP32, rotation route: the FP64 values of Km, cz, wz, thdt, zr and p0
   const double *pop;  // N x D  FP64 population map applied to the state after exp(U E dt)
   const double *popc; // N
 };

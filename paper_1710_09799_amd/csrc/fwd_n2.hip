@@ -2,6 +2,7 @@
 #include <type_traits>
 
 #include "fwd_quad.hpp"
+#include "fwd_lane.hpp"
 #include "fwd_wave.hpp"
 
 namespace mln {
@@ -23,13 +24,12 @@ hipError_t launch_fwd_n2(int route, bool comp, bool cf, const FwdArgs<Real> &a, 
   if (comp) {
     if constexpr (std::is_same<Real, float>::value) {
       if (route != ROUTE_ROT) return hipErrorInvalidValue;
-      const bool many = many_tiles(nblocks);
-      if (cf && many)
+      if (cf && many_tiles(nblocks))
         hipLaunchKernelGGL((fwd_tile_kernel_many<2, float, true, true>), dim3((unsigned)nblocks), dim3(W), 0, st, a);
       else if (cf)
         hipLaunchKernelGGL((fwd_tile_kernel<2, float, ROUTE_ROT, true, true>), dim3((unsigned)nblocks), dim3(W), 0, st, a);
-      else if (many)
-        hipLaunchKernelGGL((fwd_tile_kernel_many<2, float, true>), dim3((unsigned)nblocks), dim3(W), 0, st, a);
+      else if (lane_better(W, nblocks, device_cus()))
+        return launch_lane<2, float, true>(W, a, nblocks, st);
       else
         hipLaunchKernelGGL((fwd_tile_kernel<2, float, ROUTE_ROT, true>), dim3((unsigned)nblocks), dim3(W), 0, st, a);
       return hipGetLastError();
@@ -38,10 +38,8 @@ hipError_t launch_fwd_n2(int route, bool comp, bool cf, const FwdArgs<Real> &a, 
   }
   switch (route) {
     case ROUTE_ROT:
-      if (many_tiles(nblocks))
-        hipLaunchKernelGGL((fwd_tile_kernel_many<2, Real, false>), dim3((unsigned)nblocks), dim3(W), 0, st, a);
-      else
-        hipLaunchKernelGGL((fwd_tile_kernel<2, Real, ROUTE_ROT, false>), dim3((unsigned)nblocks), dim3(W), 0, st, a);
+      if (lane_better(W, nblocks, device_cus())) return launch_lane<2, Real, false>(W, a, nblocks, st);
+      hipLaunchKernelGGL((fwd_tile_kernel<2, Real, ROUTE_ROT, false>), dim3((unsigned)nblocks), dim3(W), 0, st, a);
       break;
     case ROUTE_DIAG: hipLaunchKernelGGL((fwd_tile_kernel<2, Real, ROUTE_DIAG, false>), dim3((unsigned)nblocks), dim3(W), 0, st, a); break;
     case ROUTE_RODR: hipLaunchKernelGGL((fwd_tile_kernel<2, Real, ROUTE_RODR, false>), dim3((unsigned)nblocks), dim3(W), 0, st, a); break;

@@ -500,19 +500,6 @@ __global__ void __launch_bounds__(LB) fwd_quad_kernel(FwdArgs<Real> a) {
   quad_tile<N, Real, COMP, CF, MF>(a, blockIdx.x);
 }
 
-// Compute units of the current device (cached per device).
-inline int quad_device_cus() {
-  static int cache[64] = {0};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-  if (!cache[dev]) {
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
-    cache[dev] = cus;
-  }
-  return cache[dev];
-}
-
 // The LB = 512 instance for tiles of at most 128 cells when every tile has a
 // compute unit of its own, for the instances whose LB = 1024 build spills
 // (FP64 and two-float fields at N = 3: 36 and 20 bytes per lane; the
@@ -524,7 +511,7 @@ hipError_t launch_quad(int W, const FwdArgs<Real> &a, int64_t nblocks, hipStream
   constexpr bool wide = std::is_same<Real, double>::value || CF;
   if (mf)
     hipLaunchKernelGGL((fwd_quad_kernel<N, Real, COMP, CF, 1024, true>), dim3((unsigned)nblocks), dim3(4 * W), 0, st, a);
-  else if (wide && 4 * W <= 512 && nblocks <= quad_device_cus())
+  else if (wide && 4 * W <= 512 && nblocks <= device_cus())
     hipLaunchKernelGGL((fwd_quad_kernel<N, Real, COMP, CF, 512>), dim3((unsigned)nblocks), dim3(4 * W), 0, st, a);
   else
     hipLaunchKernelGGL((fwd_quad_kernel<N, Real, COMP, CF, 1024>), dim3((unsigned)nblocks), dim3(4 * W), 0, st, a);

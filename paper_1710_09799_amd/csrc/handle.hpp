@@ -60,6 +60,7 @@ struct mln_handle {
   bool wave = false;                  // single-wavefront tile kernel (W = 64 * C cells)
   bool quad = false;                  // four-lanes-per-cell tile kernel (W cells, 4 W threads)
   bool qmf = false;                   // ... with the shared-factor product on the matrix cores
+  bool adjoint = false;               // created with checkpoints or the whole tape
   bool streamed = false;              // one step per launch, state streamed through HBM
   int64_t ntiles = 0;
   int rs = 8;  // bytes per real of the state

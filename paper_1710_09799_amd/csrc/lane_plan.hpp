@@ -1,0 +1,70 @@
+// lane_plan.hpp -- when the one-wavefront tile kernel (fwd_lane.hpp) runs and
+// with which tile.  Host code, no device calls.
+#pragma once
+
+#include <algorithm>
+#include <cstdint>
+
+namespace mln {
+
+// Tiles of W cells on one wavefront (W / 64 cells per lane) or on W / 64
+// wavefronts of the one-cell-per-thread kernel.  A lane's step is as long as
+// its cells, so tiles of four cells per lane need about three wavefronts per
+// compute unit to win (three-level FP64, 256 cells and 24 steps: 721 tiles
+// 7.1e10 against 7.2e10 cell-updates/s, 289 tiles 2.9e10 against 3.5e10), and
+// from there on they do (5042 tiles 1.46e11 against 9.2e10); tiles of one or
+// two cells per lane always do (128 cells, 24 steps: 500 tiles 3.3e10 against
+// 2.5e10; 64 cells, 12 steps: 1000 tiles 3.8e10 against 2.4e10).
+inline bool lane_better(int W, int64_t ntiles, int cus) { return W <= 128 || ntiles >= 3 * (int64_t)cus; }
+
+// Smallest grid that the automatic choice gives to the one-wavefront kernel
+// (four lanes per cell below): where the measured rates cross,
+// cell-updates/s lane / quad.  Two-level: FP64 and the compensated state 4000
+// cells 4.7e9 / 4.1e9, 20000 cells 2.2e10 / 1.7e10; FP32 12000 cells 1.46e10 /
+// 1.44e10.  Three-level: FP64 24000 cells 2.7e10 / 2.5e10 (at 20000 cells the
+// four-lane kernel's 228 tiles just fit the compute units: 2.3e10 / 2.7e10);
+// FP32 30000 cells 3.9e10 / 4.6e10, 36000 cells 4.1e10 / 3.8e10; compensated
+// (its product on the matrix cores) 36000 cells 3.2e10 / 3.2e10, 50000 cells
+// 3.9e10 / 3.7e10.
+inline int64_t lane_min_cells(int N, bool fp32_plain, bool comp) {
+  if (N == 2) return fp32_plain ? 12000 : 3000;
+  return fp32_plain ? 33000 : (comp ? 40000 : 23000);
+}
+
+struct LanePlan {
+  int W, K;  // cells per tile, steps per launch
+};
+
+// Tile and steps per launch from a model of a launch: a fixed 2.3 us, K steps
+// of the busiest SIMD (n wavefronts on it: the latency L of one wavefront's
+// step, or n times its issue time I) and half of the launch's memory time
+// (the other half overlaps).  L and I in us for 1, 2 and 4 cells per lane,
+// fitted to runs of 4000 to 4 million cells; the choice is within a few
+// percent of the best shape there.
+inline LanePlan lane_plan(int N, bool fp32_plain, int state_bytes, int64_t nx, int cus) {
+  static const double L[2][2][3] = {{{0.34, 0.47, 0.74}, {0.30, 0.40, 0.60}}, {{0.73, 1.09, 2.02}, {0.52, 0.90, 1.63}}};
+  static const double I[2][2][3] = {{{0.15, 0.22, 0.40}, {0.10, 0.14, 0.27}}, {{0.56, 0.80, 1.50}, {0.28, 0.54, 1.07}}};
+  static const int C[3] = {1, 2, 4};
+  const int ni = N == 2 ? 0 : 1, pi = fp32_plain ? 1 : 0;
+  LanePlan best{256, 24};
+  double best_t = 0.0;
+  for (int c = 0; c < 3; ++c) {
+    const int W = 64 * C[c];
+    for (int K = 8; K <= (W == 64 ? 28 : W * 3 / 8); K += 4) {
+      const int64_t owned = W - 2 * K, tiles = (nx + owned - 1) / owned;
+      const double n = (double)tiles / (4.0 * cus);
+      // up to four wavefronts share a SIMD at once; beyond that they follow each other
+      const double w = n <= 1.0 ? 1.0 : (n <= 4.0 ? (double)(int64_t)(n + 0.999999) : n + 0.4);
+      const double step = std::max(L[ni][pi][c], n <= 1.0 ? 0.0 : w * I[ni][pi][c]);
+      const double mem = (double)nx * (1.0 + (double)K / (double)owned) * 2.0 * state_bytes / 4.9e6;
+      const double t = (2.3 + K * step + 0.5 * mem) / K;
+      if (best_t == 0.0 || t < best_t) {
+        best_t = t;
+        best = {W, K};
+      }
+    }
+  }
+  return best;
+}
+
+}  // namespace mln

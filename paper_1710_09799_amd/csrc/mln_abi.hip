@@ -167,9 +167,21 @@ int mln::upload_factors(const Factors &f, int route, double dt, DevBuf &fac, Dev
   };
   const std::vector<double> &cvec = rot ? f.rz : f.c;
   size_t oKl = push(lo_of(Km)), ocl = push(lo_of(cvec)), otl = push(lo_of(thdt));
+  // the FP64 block of the single-precision handles (CellFac)
+  size_t o64 = 0;
+  if (rot && sizeof(Real) == 4) {
+    std::vector<double> v(Km);
+    for (const std::vector<double> *x : {&f.rz, &f.wz, (const std::vector<double> *)&thdt, &f.zr})
+      v.insert(v.end(), x->begin(), x->end());
+    v.push_back(f.pr);
+    o64 = blk.size();  // a multiple of 16 floats
+    blk.resize(o64 + 2 * v.size());
+    std::memcpy(blk.data() + o64, v.data(), v.size() * sizeof(double));
+  }
   HIP_TRY(fac.alloc(blk.size() * sizeof(Real)));
   HIP_TRY(hipMemcpy(fac.p, blk.data(), blk.size() * sizeof(Real), hipMemcpyHostToDevice));
   const Real *b = (const Real *)fac.p;
+  fd.blk64 = o64 ? (const double *)(b + o64) : nullptr;
   fd.Km = b + oK;
   fd.cz = b + oc;
   fd.wz = b + ow;
@@ -315,13 +327,16 @@ int set_kernel(mln_handle *h, int variant_req, int tile, int steps_per_launch) {
     return MLN_OK;
   }
   h->streamed = false;
-  // automatic choice: four lanes per cell while the grid is too small to
-  // fill the chip with one cell per thread (the step is latency-bound there,
-  // and four lanes give four times the wavefronts); one cell per thread on
-  // large grids, where the quad's replicated field work costs issue slots
-  // (measured crossover near 1e5 cells at N = 2, 3)
+  // automatic choice: four lanes per cell on grids too small to fill the chip
+  // otherwise (the step is latency-bound there, and four lanes give four
+  // times the wavefronts); from lane_min_cells on one-wavefront tiles, where
+  // the quad's replicated field work costs issue slots.  Float-float fields,
+  // and handles with an adjoint, whose reverse kernel overlaps the four-lane
+  // launches: four lanes up to 1e5 cells, then one cell per thread.
+  const bool lane = rot && h->f.N <= 3 && !h->cf && !h->adjoint;
   if (variant == 0) {
-    variant = !rot ? 1 : (h->f.N <= 3 ? (h->grid.nx < kQuadMaxAutoCells ? 3 : 1) : (h->f.N == 4 && !h->cf ? 2 : 1));
+    const int64_t from = lane ? lane_min_cells(h->f.N, h->prec == MLN_FP32, h->comp) : kQuadMaxAutoCells;
+    variant = !rot ? 1 : (h->f.N <= 3 ? (h->grid.nx < from ? 3 : 1) : (h->f.N == 4 && !h->cf ? 2 : 1));
     // the matrix-core product pays off with the compensated state at N = 3
     // and with compensated fields (measured; FP64 and plain FP32 run faster
     // on the DPP product, whose FMA chain is shorter than the MFMA latency)
@@ -383,6 +398,12 @@ int set_kernel(mln_handle *h, int variant_req, int tile, int steps_per_launch) {
         K = k;
         break;
       }
+  }
+  if (lane && variant == 1 && tile <= 0 && steps_per_launch <= 0) {
+    const LanePlan p = lane_plan(h->f.N, h->prec == MLN_FP32, h->rs * (2 + h->f.D * (h->comp ? 2 : 1)), h->grid.nx,
+                                 device_cus());
+    h->W = p.W;
+    K = p.K;
   }
   if (2 * K >= h->W || K > kMaxStepsPerLaunch)
     return set_err(MLN_EINVAL, "steps_per_launch must be below tile/2 (and at most 128)");
@@ -620,6 +641,7 @@ int mln_init(const mln_medium *medium, const mln_grid *grid, const mln_source *s
   h->fd_coef[4] = (cl * grid->dt - grid->dx) / (cl * grid->dt + grid->dx);
   h->fd_coef[5] = -2.0 * sg / (1.0 + sg);
   tune_fp32_coefs(h.get());
+  h->adjoint = opt.ckpt_every != 0;
   rc = set_kernel(h.get(), opt.variant, opt.tile, opt.steps_per_launch);
   if (rc) return rc;
   h->nmed = grid->med_end - grid->med_begin;
@@ -755,7 +777,8 @@ int mln_tune(mln_handle *h, int32_t trial_steps, int32_t *variant, int32_t *tile
                                 {3, 256, 32}, {1, 64, 8},   {1, 128, 8},  {1, 128, 16}, {1, 128, 32},
                                 {1, 256, 8},  {1, 256, 16}, {1, 256, 32}, {2, 64, 8},   {2, 128, 16},
                                 {2, 256, 32}, {4, 256, 1},  {5, 64, 8},   {5, 128, 16}, {5, 128, 20},
-                                {5, 128, 0},  {5, 128, 32}, {5, 256, 16}, {5, 256, 32}};
+                                {5, 128, 0},  {5, 128, 32}, {5, 256, 16}, {5, 256, 32}, {1, 64, 12},
+                                {1, 64, 16},  {1, 64, 20},  {1, 64, 24},  {1, 128, 12}, {1, 128, 24}, {1, 256, 24}};
   const KernelChoice start = save_kernel(h);
   KernelChoice best_k = start;
   double best = INFINITY;

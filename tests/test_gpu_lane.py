@@ -1,0 +1,93 @@
+"""The one-wavefront tile kernel (variant "block" with plain fields: tiles of
+64 and 128 cells always, of 192 and 256 cells from three per compute unit on)
+against the oracle: tiles with ragged ends, media that begin and end inside a
+tile, halos that are no multiple of the cells per lane, and rotation angles
+beyond the short series.
+
+err_E = max |E - E_oracle| / max |E_oracle|, err_pop = max |rho_aa - oracle|.
+Tolerances: FP64 1e-10, single precision 1e-5 (the bars of the other kernels).
+"""
+import numpy as np
+import pytest
+
+from paper_1710_09799_amd import mln
+from paper_1710_09799_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+TOL = {"fp64": 1e-10, "fp32c": 1e-5, "fp32": 1e-5}
+
+
+def _errs(got, ref):
+    e = np.concatenate([got["e_snap"].ravel(), got["probe"]])
+    er = np.concatenate([ref["e_snap"].ravel(), ref["probe"]])
+    err_p = np.max(np.abs(got["pop"] - ref["pop"])) if ref["pop"].size else 0.0
+    return np.max(np.abs(e - er)) / np.max(np.abs(er)), err_p
+
+
+@pytest.fixture(scope="module")
+def refs(orc):
+    cache = {}
+
+    def get(key, problem, snap):
+        if key not in cache:
+            cache[key] = orc.run(problem, snap_every=snap)
+        return cache[key]
+    return get
+
+
+@pytest.mark.parametrize("n", [2, 3])
+@pytest.mark.parametrize("precision", ["fp64", "fp32c", "fp32"])
+@pytest.mark.parametrize("tile,k", [(64, 7), (64, 28), (128, 15), (128, 24)])
+@pytest.mark.parametrize("nx,med", [(3, (1, 2)), (65, None), (208, (63, 130)), (417, (5, 5))])
+def test_lane_tiles(refs, n, precision, tile, k, nx, med):
+    p = W.random_problem(n, 40 + n, nx=nx, nt=200, med=med)
+    print(f"[case] lane n={n} {precision} tile={tile} k={k} nx={nx} med={med}", flush=True)
+    got = mln.run(p, precision=precision, snap_every=33, variant="block", tile=tile, steps_per_launch=k)
+    ee, ep = _errs(got, refs((n, nx, med), p, 33))
+    assert ee < TOL[precision] and ep < TOL[precision], (ee, ep)
+
+
+@pytest.mark.parametrize("n", [2, 3])
+@pytest.mark.parametrize("precision", ["fp64", "fp32c", "fp32"])
+@pytest.mark.parametrize("tile,k", [(192, 90), (256, 121)])
+def test_lane_wide_tiles(refs, n, precision, tile, k):
+    """Three and four cells per lane: enough tiles by narrow owned parts."""
+    nx = 11003
+    p = W.random_problem(n, 50 + n, nx=nx, nt=130, med=(70, nx - 131))
+    print(f"[case] lane n={n} {precision} tile={tile} k={k}", flush=True)
+    got = mln.run(p, precision=precision, snap_every=65, variant="block", tile=tile, steps_per_launch=k)
+    ee, ep = _errs(got, refs((n, "wide"), p, 65))
+    assert ee < TOL[precision] and ep < TOL[precision], (ee, ep)
+
+
+@pytest.mark.parametrize("n", [2, 3])
+@pytest.mark.parametrize("scale", [30.0, 1000.0, 30000.0])
+def test_lane_wide_angles(refs, n, scale):
+    """Fields that turn a cell by up to about 1/4, 10 and 300 rad per step."""
+    p = W.random_problem(n, 60 + n, nx=150, nt=120)
+    p.source.amplitude *= scale
+    got = mln.run(p, precision="fp64", snap_every=30, variant="block", tile=64, steps_per_launch=16)
+    ee, ep = _errs(got, refs((n, scale), p, 30))
+    print(f"[case] lane angles n={n} scale={scale} err_E={ee:.1e} err_pop={ep:.1e}", flush=True)
+    assert ee < 1e-10 and ep < 1e-10, (ee, ep)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32c"])
+def test_lane_automatic_choice_and_chunks(precision):
+    """A grid beyond the crossover takes the kernel by itself and agrees with
+    the four-lane kernel; stepping in uneven chunks changes nothing."""
+    p = W.three_level(nx=45000, nt=300)
+    s = mln.Solver(p, precision=precision, snap_every=100)
+    assert s.config()["variant"] == "block"
+    a = {k: v.cpu().numpy().copy() for k, v in s.run().items()}
+    s.reset()
+    for k in (1, 37, 100, 162):
+        s.step(k)
+    b = {k: v.cpu().numpy() for k, v in s.run().items()}
+    for k in a:
+        assert np.array_equal(a[k], b[k]), k
+    s.close()
+    q = mln.run(p, precision=precision, snap_every=100, variant="quad", tile=128, steps_per_launch=20)
+    ee, ep = _errs(a, q)
+    tol = 1e-12 if precision == "fp64" else 1e-5
+    assert ee < tol and ep < tol, (ee, ep)
