@@ -171,8 +171,7 @@ int configure(mln_batch *b, int variant, int W, int K) {
     h->wave = false;
     h->W = W;
     h->halo = K;
-    h->owned = W - 2 * K;
-    h->ntiles = (h->grid.nx + h->owned - 1) / h->owned;
+    set_owned(h);
   }
   b->variant = variant;
   b->W = W;

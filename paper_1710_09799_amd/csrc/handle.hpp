@@ -129,6 +129,17 @@ struct mln_handle {
 
 namespace mln {
 
+// Owned cells of the tiles and their number for tiles of h->W cells and
+// h->halo steps per launch.  The last cell (Mur) needs the new E of its left
+// neighbour, one cell deeper into the halo than the others, so it must not be
+// a tile's first owned cell.
+inline void set_owned(mln_handle *h) {
+  h->owned = h->W - 2 * h->halo;
+  const int unit = h->owned % 4 == 0 ? 4 : (h->owned % 2 == 0 ? 2 : 1);  // keeps the runs of cells per lane whole
+  while ((h->grid.nx - 1) % h->owned == 0 && h->owned > 1) h->owned = h->owned > unit ? h->owned - unit : h->owned - 1;
+  h->ntiles = (h->grid.nx + h->owned - 1) / h->owned;
+}
+
 // Restore the initial state (step 0) of the handle.  Synchronises the stream.
 int reset_state(mln_handle *h);
 // The host's part of it: step 0, slot 0, no checkpoints.

@@ -410,8 +410,7 @@ int set_kernel(mln_handle *h, int variant_req, int tile, int steps_per_launch) {
   if (pade_wave && pade_lds_bytes(h->f.N, h->rs, h->W) > kPadeMaxLds)
     return set_err(MLN_EINVAL, "tile too large for the LDS of the per-step Pade kernel");
   h->halo = K;
-  h->owned = h->W - 2 * K;
-  h->ntiles = (h->grid.nx + h->owned - 1) / h->owned;
+  set_owned(h);
   return MLN_OK;
 }
 

@@ -91,3 +91,26 @@ def test_lane_automatic_choice_and_chunks(precision):
     ee, ep = _errs(a, q)
     tol = 1e-12 if precision == "fp64" else 1e-5
     assert ee < tol and ep < tol, (ee, ep)
+
+
+@pytest.mark.parametrize("variant,tile,k,precision", [("quad", 64, 20, "fp64"), ("block", 64, 7, "fp64"),
+                                                      ("block", 128, 24, "fp32c"), ("block", 256, 32, "fp32cf"),
+                                                      ("wave", 64, 8, "fp64"), ("quad_mfma", 64, 20, "fp32c")])
+def test_last_cell_at_a_tile_boundary(orc, variant, tile, k, precision):
+    """Grids on which the last cell (whose boundary condition reaches two
+    cells back) would be a tile's first owned cell, and its neighbours."""
+    for nx in (3 * (tile - 2 * k), 3 * (tile - 2 * k) + 1):
+        p = W.random_problem(3, 7, nx=nx, nt=2 * nx + 100)
+        ee, ep = _errs(mln.run(p, precision=precision, snap_every=60, variant=variant, tile=tile, steps_per_launch=k),
+                       orc.run(p, snap_every=60))
+        assert ee < (1e-12 if precision == "fp64" else 1e-5), (nx, ee)
+
+
+def test_batch_last_cell_at_a_tile_boundary(orc):
+    probs = [W.random_problem(2 + i % 2, 80 + i, nx=33 + 16 * i, nt=300) for i in range(4)]
+    b = mln.Batch(probs, precision="fp64", snap_every=100, variant="block", tile=64, steps_per_launch=16)
+    outs = b.run()
+    for p, o in zip(probs, outs):
+        ee, ep = _errs({q: v.cpu().numpy() for q, v in o.items()}, orc.run(p, snap_every=100))
+        assert ee < 1e-12 and ep < 1e-10, (p.grid.nx, ee, ep)
+    b.close()
