@@ -1259,6 +1259,10 @@ int mln_grad(mln_handle *h, const double *dJ_dprobe, mln_grads *out) {
     rowned = rW - 2 * rhalo;
     rtiles = (h->grid.nx + rowned - 1) / rowned;
   }
+  // backwards the last cell (Mur) reaches two cells to its left in a step, so
+  // it must not be the first cell beyond a tile
+  while (h->grid.nx - 1 > rhalo && (h->grid.nx - 1 - rhalo) % rowned == 0 && rowned > 1) --rowned;
+  rtiles = (h->grid.nx + rowned - 1) / rowned;
   if (!h->gprobe.p) {
     for (int b = 0; b < 2; ++b) {
       HIP_TRY(h->lE[b].alloc(rs * h->grid.nx));

@@ -114,3 +114,20 @@ def test_batch_last_cell_at_a_tile_boundary(orc):
         ee, ep = _errs({q: v.cpu().numpy() for q, v in o.items()}, orc.run(p, snap_every=100))
         assert ee < 1e-12 and ep < 1e-10, (p.grid.nx, ee, ep)
     b.close()
+
+
+@pytest.mark.parametrize("variant,tile,k", [("quad", 64, 7), ("block", 64, 7), ("quad", 128, 5)])
+def test_adjoint_last_cell_beyond_a_tile(orc, variant, tile, k):
+    """Grids on which the last cell would be the first beyond a reverse tile."""
+    for nx in (2 * (tile - 2 * k) + k + 1, 2 * (tile - 2 * k) + k):
+        p = W.random_problem(3, 7, nx=nx, nt=400)
+        gp = 2.0 * p.grid.dt * orc.run(p)["probe"]
+        ref = orc.grad(p, gp)
+        s = mln.Solver(p, ckpt_every=100)
+        s.configure_adjoint(variant, tile, k)
+        s.run()
+        g = s.grad(gp)
+        s.close()
+        for q in ref:
+            dev = np.max(np.abs(np.asarray(g[q]) - np.asarray(ref[q]))) / np.max(np.abs(ref[q]))
+            assert dev < 1e-9, (nx, q, dev)
