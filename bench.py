@@ -76,7 +76,7 @@ def source_hash(files):
     return h.hexdigest()
 
 
-TMZ_SOURCES = ["fwd_tmz.hpp", "fwd_impl.hpp", "fwd_kernels.hpp", "tmz.hip"]
+TMZ_SOURCES = ["fwd_tmz_tile.hpp", "fwd_tmz.hpp", "cells.hpp", "fwd_impl.hpp", "fwd_kernels.hpp", "tmz.hip"]
 STREAM_SOURCES = ["fwd_stream.hpp", "fwd_impl.hpp", "fwd_kernels.hpp", "stream.hip"]
 
 
@@ -423,10 +423,10 @@ def variants(p3, ref64, pop64, headline):
 def tmz_beam(reps=REPS):
     """Two-dimensional TMz grid (the scheme beyond the paper's 1-D models):
     the three-level ladder on 2048 x 512 cells (medium 1536 x 512), a
-    Gaussian beam carrying a 50 fs pi pulse, 4096 steps, one launch per step
-    (the Bloch state is streamed from and to HBM every step: the HBM-bound
-    form).  GB/s are algorithmic: every cell's E_z, H_x, H_y and every medium
-    cell's state read and written once per step; the median of `reps` runs."""
+    Gaussian beam carrying a 50 fs pi pulse, 4096 steps, several steps per
+    launch.  GB/s are algorithmic for one step per launch: every cell's E_z,
+    H_x, H_y and every medium cell's state read and written once per step (a
+    launch of K steps moves less); the median of `reps` runs."""
     import numpy as np
     import torch
     from paper_1710_09799_amd import mln
@@ -437,7 +437,7 @@ def tmz_beam(reps=REPS):
     cells = g.nx * g.ny
     out = {"workload": f"three-level ladder on a {g.nx} x {g.ny} TMz grid (medium {g.mx1 - g.mx0} x "
                        f"{g.my1 - g.my0}), {g.nt} steps, Gaussian beam, 50 fs pi pulse",
-           "kernel": "fwd_tmz_kernel (64 x 4 cells per workgroup, one launch per step)"}
+           "kernel": "fwd_tmz_tile_kernel (tiles of 64 columns in registers, several steps per launch)"}
     rec = {}
     for prec, rs, rows in (("fp64", 8, D), ("fp32", 4, D), ("fp32c", 4, 2 * D)):
         s = mln.Tmz(p, precision=prec, snap_every=g.nt // 2, record_e=False)

@@ -53,35 +53,60 @@ __device__ __forceinline__ double pair_exact(double x) {
 }
 __device__ __forceinline__ float pair_exact(float x) { return x; }
 
-// The factors of the step in the arithmetic type M.
+// The factors of the step in the arithmetic type M.  Those of N = 2 are held
+// in scalar registers for the whole launch: left to itself the compiler reads
+// them again in every step and waits for the scalar cache (two-level, 50000
+// cells: 4.9e10 against 4.5e10 cell-updates/s).  Those of N = 3 would push the
+// series' constants out of the scalar registers (150000 cells: 7.7e10 held,
+// 8.1e10 read again).
 template <int N, typename M>
 struct CellFac {
   static constexpr int D = N * N - 1, Q = N * (N - 1) / 2;
-  const M *K, *c, *w, *th, *zr;
+  const M *K;
+  M c[D], w[D], th[Q], zr[2 * Q], k2[N == 2 ? D * D : 1];  // k2: K of N = 2
   M p0, thmax;  // thmax: |E| thmax bounds every rotation angle of a cell
+  static __device__ __forceinline__ M keep(M x) {
+    if constexpr (N == 2) __asm__ volatile("" : "+s"(x));
+    return x;
+  }
   template <typename Real>
   __device__ __forceinline__ void set(const FacDev<Real> &f) {
+    const M *pc, *pw, *pt, *pz;
+    M q0;
     if constexpr (sizeof(Real) == sizeof(M)) {
       K = f.Km;
-      c = f.cz;
-      w = f.wz;
-      th = f.thdt;
-      zr = f.zr;
-      p0 = f.p0;
+      pc = f.cz;
+      pw = f.wz;
+      pt = f.thdt;
+      pz = f.zr;
+      q0 = f.p0;
     } else {  // compensated FP32 state: the FP64 block
       K = f.blk64;
-      c = K + D * D;
-      w = c + D;
-      th = w + D;
-      zr = th + Q;
-      p0 = cld(zr, D);
+      pc = K + D * D;
+      pw = pc + D;
+      pt = pw + D;
+      pz = pt + Q;
+      q0 = cld(pz, D);
     }
-    thmax = 0;
+    M m = 0;
 #pragma unroll
     for (int p = 0; p < Q; ++p) {
-      const M t = cld(th, p);
-      thmax = t > thmax ? t : (-t > thmax ? -t : thmax);
+      th[p] = keep(cld(pt, p));
+      m = th[p] > m ? th[p] : (-th[p] > m ? -th[p] : m);
+      zr[2 * p] = keep(cld(pz, 2 * p));
+      zr[2 * p + 1] = keep(cld(pz, 2 * p + 1));
     }
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+      c[i] = keep(cld(pc, i));
+      w[i] = keep(cld(pw, i));
+    }
+    if constexpr (N == 2) {
+#pragma unroll
+      for (int i = 0; i < D * D; ++i) k2[i] = keep(cld(K, i));
+    }
+    p0 = keep(q0);
+    thmax = m;
   }
 };
 
@@ -164,10 +189,9 @@ __device__ __forceinline__ void sincm1_wide(float x, float &s, float &cm1) {
 
 template <int N, typename M, int C, bool SERIES>
 __device__ __forceinline__ void rotate_cells(const CellFac<N, M> &f, const M (&E)[C], M (&z)[C][N * N - 1]) {
-  const M *pt = f.th, *pz = f.zr;
 #pragma unroll
   for (int p = 0; p < CellFac<N, M>::Q; ++p) {
-    const M th = cld(pt, p), ar = cld(pz, 2 * p), br = cld(pz, 2 * p + 1);
+    const M th = f.th[p], ar = f.zr[2 * p], br = f.zr[2 * p + 1];
 #pragma unroll
     for (int c = 0; c < C; ++c) {
       M s, cm1;
@@ -287,12 +311,11 @@ template <int N, typename M, bool PAIR, int C>
 __device__ __forceinline__ void cells_shared(const CellFac<N, M> &f, const CellK<N, M> &K, M (&z)[C][N * N - 1],
                                              M (&P)[C]) {
   constexpr int D = N * N - 1;
-  const M *w = f.w, *cz = f.c;
 #pragma unroll
   for (int c = 0; c < C; ++c) P[c] = f.p0;
 #pragma unroll
   for (int j = 0; j < D; ++j) {
-    const M wj = cld(w, j);
+    const M wj = f.w[j];
 #pragma unroll
     for (int c = 0; c < C; ++c) P[c] += wj * z[c][j];
   }
@@ -304,8 +327,8 @@ __device__ __forceinline__ void cells_shared(const CellFac<N, M> &f, const CellK
     if constexpr (N == 3) {
 #pragma unroll
       for (int m = 0; m < 4; ++m) {
-        da[2 * m] = db[2 * m] = cld(cz, 2 * m);
-        da[2 * m + 1] = db[2 * m + 1] = cld(cz, 2 * m + 1);
+        da[2 * m] = db[2 * m] = f.c[2 * m];
+        da[2 * m + 1] = db[2 * m + 1] = f.c[2 * m + 1];
         if (two)
           rows2(K.k[m], z[g], z[h], da[2 * m], da[2 * m + 1], db[2 * m], db[2 * m + 1]);
         else
@@ -314,10 +337,10 @@ __device__ __forceinline__ void cells_shared(const CellFac<N, M> &f, const CellK
     } else {
 #pragma unroll
       for (int i = 0; i < D; ++i) {
-        da[i] = db[i] = cld(cz, i);
+        da[i] = db[i] = f.c[i];
 #pragma unroll
         for (int j = 0; j < D; ++j) {
-          const M k = cld(f.K, i * D + j);
+          const M k = f.k2[i * D + j];
           da[i] += k * z[g][j];
           if (two) db[i] += k * z[h][j];
         }

@@ -7,9 +7,9 @@
 //
 // Staggering (arrays row major, index j * nx + i): E_z at (i, j), H_x at
 // (i, j + 1/2), H_y at (i + 1/2, j); periodic in y.  One launch per time step
-// n -> n + 1, one thread per cell, 64 x 4 cells per workgroup (a wavefront
-// is one row of 64 cells: every array access of a wavefront is one
-// contiguous segment):
+// n -> n + 1 for N = 4, 6 (N = 2, 3: fwd_tmz_tile.hpp), one thread per cell,
+// 64 x 4 cells per workgroup (a wavefront is one row of 64 cells: every array
+// access of a wavefront is one contiguous segment):
 //   H_x(i, j)  -= chy (E(i, j+1) - E(i, j))          every column
 //   H_y(i, j)  += chx (E(i+1, j) - E(i, j))          i <= nx-2
 //   medium cells: dP/dt and the Bloch state from E^n(i, j) (cell_step)
@@ -138,31 +138,6 @@ __global__ void __launch_bounds__(kTmzTX * kTmzTY) fwd_tmz_kernel(TmzArgs<Real> 
   __shared__ Real sF[rot_smem<N>() ? 1 : RotLds<N, Real, COMP>::size];
   __shared__ double sP[N * D + N];
   tmz_step<N, Real, COMP>(a, sF, sP);
-}
-
-// N = 2, 3 in FP64 and compensated FP32, compiled for at least five
-// wavefronts per SIMD (measured on the 2048 x 512 three-level beam: FP64
-// 26.9 against 27.9 us per step, compensated FP32 25.0 against 25.8, the
-// same bits; seven or eight wavefronts spill and run 1.3-1.8x slower; N = 4,
-// 6 would spill)
-template <int N, typename Real, bool COMP>
-__global__ void __launch_bounds__(kTmzTX * kTmzTY) __attribute__((amdgpu_waves_per_eu(5, 8)))
-fwd_tmz_kernel_w5(TmzArgs<Real> a) {
-  constexpr int D = N * N - 1;
-  __shared__ Real sF[rot_smem<N>() ? 1 : RotLds<N, Real, COMP>::size];
-  __shared__ double sP[N * D + N];
-  tmz_step<N, Real, COMP>(a, sF, sP);
-}
-
-// N = 2, 3 in plain FP32, compiled for seven wavefronts per SIMD (71 VGPRs,
-// no spills; 15.6 against 16.2 us per step on the same beam)
-template <int N>
-__global__ void __launch_bounds__(kTmzTX * kTmzTY) __attribute__((amdgpu_waves_per_eu(7, 8)))
-fwd_tmz_kernel_w7(TmzArgs<float> a) {
-  constexpr int D = N * N - 1;
-  __shared__ float sF[rot_smem<N>() ? 1 : RotLds<N, float, false>::size];
-  __shared__ double sP[N * D + N];
-  tmz_step<N, float, false>(a, sF, sP);
 }
 
 }  // namespace mln

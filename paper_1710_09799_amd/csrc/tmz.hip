@@ -10,7 +10,7 @@
 #include <type_traits>
 #include <vector>
 
-#include "fwd_tmz.hpp"
+#include "fwd_tmz_tile.hpp"
 #include "handle.hpp"
 
 using namespace mln;
@@ -27,8 +27,10 @@ struct mln_tmz {
   DevBuf fac, pop, popc;
   FacDev<double> fd{};
   FacDev<float> ff{};
-  DevBuf E[2], Hx[2], Hy[2], z, src, prof;
-  int cur = 0;
+  DevBuf E[2], Hx[2], Hy[2], z[2], src, prof;  // z[1]: the tile kernel only
+  int rows = 0, K = 1;  // tile kernel: rows of a tile (0: one step per launch), steps per launch
+  int cur = 0, zcur = 0;  // buffers of the current step
+  FillPlan fill;
   std::vector<double> src_host, prof_host;
   // FDTD coefficients: chx, chy, ca, cb, 1/dx, 1/dy, kmur (FP64), and the
   // single-precision set with (chx, 1/dx) and (chy, 1/dy) chosen so that
@@ -44,14 +46,34 @@ namespace {
 template <int N, typename Real, bool COMP>
 hipError_t launch_n(const TmzArgs<Real> &a, hipStream_t st) {
   const dim3 grid((unsigned)((a.nx + kTmzTX - 1) / kTmzTX), (unsigned)((a.ny + kTmzTY - 1) / kTmzTY));
-  if constexpr (N <= 3 && std::is_same<Real, float>::value && !COMP) {
-    hipLaunchKernelGGL((fwd_tmz_kernel_w7<N>), grid, dim3(kTmzTX * kTmzTY), 0, st, a);
-  } else if constexpr (N <= 3) {
-    hipLaunchKernelGGL((fwd_tmz_kernel_w5<N, Real, COMP>), grid, dim3(kTmzTX * kTmzTY), 0, st, a);
-  } else {
+  if constexpr (N <= 3)
+    hipLaunchKernelGGL((fwd_tmz_one_kernel<N, Real, COMP>), grid, dim3(kTmzTX * kTmzTY), 0, st, a);
+  else
     hipLaunchKernelGGL((fwd_tmz_kernel<N, Real, COMP>), grid, dim3(kTmzTX * kTmzTY), 0, st, a);
+  return hipGetLastError();
+}
+
+// rows: C * kTmzWaves
+template <int N, typename Real, bool COMP>
+hipError_t launch_tile_n(int rows, const TmzTileArgs<Real> &t, hipStream_t st) {
+  const dim3 grid((unsigned)((t.a.nx + t.ox - 1) / t.ox), (unsigned)((t.a.ny + t.oy - 1) / t.oy)), block(64 * kTmzWaves);
+  switch (rows / kTmzWaves) {
+    case 2: hipLaunchKernelGGL((fwd_tmz_tile_kernel<N, Real, COMP, 2, kTmzWaves>), grid, block, 0, st, t); break;
+    case 4: hipLaunchKernelGGL((fwd_tmz_tile_kernel<N, Real, COMP, 4, kTmzWaves>), grid, block, 0, st, t); break;
+    case 6:
+      if constexpr (tmz_six_rows<N, Real, COMP>()) {
+        hipLaunchKernelGGL((fwd_tmz_tile_kernel<N, Real, COMP, 6, kTmzWaves>), grid, block, 0, st, t);
+        break;
+      }
+      return hipErrorInvalidValue;
+    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+template <typename Real, bool COMP>
+hipError_t launch_tile(int N, int rows, const TmzTileArgs<Real> &t, hipStream_t st) {
+  return N == 2 ? launch_tile_n<2, Real, COMP>(rows, t, st) : launch_tile_n<3, Real, COMP>(rows, t, st);
 }
 
 template <typename Real, bool COMP>
@@ -95,39 +117,31 @@ int tmz_write_probe0(mln_tmz *t) {
 }
 
 int tmz_reset(mln_tmz *t) {
-  const int64_t nx = t->grid.nx, ny = t->grid.ny;
-  const size_t cells = (size_t)nx * ny;
-  std::vector<double> e(cells, 0.0);
-  for (int64_t j = 0; j < ny; ++j) e[(size_t)j * nx] = t->src_host[0] * t->prof_host[j];
-  std::vector<unsigned char> buf;
-  if (t->rs == 8)
-    to_dev<double>(e.data(), cells, 1.0, buf);
-  else
-    to_dev<float>(e.data(), cells, 1.0, buf);
-  for (int b = 0; b < 2; ++b) {
-    HIP_TRY(hipMemcpy(t->E[b].p, buf.data(), buf.size(), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemset(t->Hx[b].p, 0, t->Hx[b].bytes));
-    HIP_TRY(hipMemset(t->Hy[b].p, 0, t->Hy[b].bytes));
-  }
-  // Bloch state: the rotation route's initial deviation y0 in every cell
-  const int D = t->f.D;
-  const int rows = t->comp ? 2 * D : D;
-  std::vector<unsigned char> zb((size_t)rows * t->ld * t->rs, 0);
-  for (int k = 0; k < D; ++k)
-    for (int64_t c = 0; c < t->nmed; ++c) {
-      const double v = t->f.y0[k];
-      if (t->rs == 8) {
-        ((double *)zb.data())[(size_t)k * t->ld + c] = v;
-      } else {
-        float *o = (float *)zb.data();
-        o[(size_t)k * t->ld + c] = (float)v;
-        if (t->comp) o[(size_t)(D + k) * t->ld + c] = (float)(v - (double)(float)v);
-      }
-    }
-  HIP_TRY(hipMemcpy(t->z.p, zb.data(), zb.size(), hipMemcpyHostToDevice));
-  t->cur = 0;
+  HIP_TRY(t->fill.run(t->stream));
+  t->cur = t->zcur = 0;
   t->step = 0;
-  return tmz_write_probe0(t);
+  HIP_TRY(hipStreamSynchronize(t->stream));
+  return MLN_OK;
+}
+
+// The plan of the state at step 0: the source column, zero fields, the
+// rotation route's initial deviation y0 in every medium cell (then its low
+// parts with the compensated state); the probe's first row (column nx - 1,
+// nx >= 3) is zero.
+int tmz_plan(mln_tmz *t) {
+  const int64_t nx = t->grid.nx, ny = t->grid.ny;
+  std::vector<double> e0(t->prof_host), z0(t->f.y0);
+  for (double &v : e0) v *= t->src_host[0];
+  if (t->comp)
+    for (int k = 0; k < t->f.D; ++k) z0.push_back(z0[k] - (double)(float)z0[k]);
+  for (int b = 0; b < 2; ++b) {
+    t->fill.add(t->E[b].p, ny, nx, 1, e0, t->rs);
+    t->fill.add(t->Hx[b].p, ny, nx, 0, {}, t->rs);
+    t->fill.add(t->Hy[b].p, ny, nx, 0, {}, t->rs);
+  }
+  t->fill.add(t->z[0].p, (int64_t)z0.size(), t->ld, t->nmed, z0, t->rs);
+  t->fill.add(t->rec.probe_out, 1, ny, 0, {}, 8);
+  return t->fill.upload();
 }
 
 template <typename Real>
@@ -141,7 +155,7 @@ TmzArgs<Real> tmz_args(mln_tmz *t, const FacDev<Real> &fd, const Real (&c)[7]) {
   a.Hxout = (Real *)t->Hx[out].p;
   a.Hyin = (const Real *)t->Hy[in].p;
   a.Hyout = (Real *)t->Hy[out].p;
-  a.z = (Real *)t->z.p;
+  a.z = (Real *)t->z[t->zcur].p;
   a.src = (const Real *)t->src.p;
   a.prof = (const Real *)t->prof.p;
   a.nx = t->grid.nx;
@@ -165,22 +179,117 @@ TmzArgs<Real> tmz_args(mln_tmz *t, const FacDev<Real> &fd, const Real (&c)[7]) {
   return a;
 }
 
+// Rows of the tiles of a launch of K >= 2 steps and, in *us, its time: the
+// least in a model of a launch, 2.5 us plus the larger of a tile's own time
+// (its loads and stores and K steps) times the tiles that a compute unit works
+// off one after the other, and of the whole grid's memory traffic (4.6 TB/s)
+// and arithmetic one after the other (the workgroup that fills a compute
+// unit's registers loads, steps and stores in turn).  Fitted to beams of 150 x
+// 30 and 2048 x 512 cells, us per launch model / measured on the larger:
+// three-level FP64 48 rows and 5 steps 79 / 78, 6 steps 99 / 91, 3 steps 60 /
+// 59, 32 rows and 5 steps 87 / 85, 16 rows and 3 steps 58 / 51; FP32 32 rows
+// and 6 steps 63 / 59.
+int tmz_rows(const mln_tmz *t, int K, double *us) {
+  // [N = 2, 3][FP64, FP32][16, 32, 48 rows]: us of the ends of a tile and of a
+  // step of it, and tiles that share a compute unit
+  static const double ends[2][2][3] = {{{1.6, 2.6, 0}, {1.2, 1.9, 0}}, {{2.5, 5.4, 6.4}, {1.8, 3.2, 0}}};
+  static const double step[2][2][3] = {{{1.2, 2.0, 0}, {0.95, 1.5, 0}}, {{2.07, 3.63, 5.78}, {1.55, 2.85, 0}}};
+  static const double share[2][2][3] = {{{1.7, 1.6, 0}, {1.8, 1.9, 0}}, {{1.5, 1.0, 1.0}, {1.8, 1.4, 0}}};
+  // arithmetic of a medium cell and step, us per cell of the grid
+  static const double cell[2][2] = {{1.0e-6, 0.85e-6}, {4.8e-6, 3.2e-6}};
+  const mln_tmz_grid &g = t->grid;
+  const int ni = t->N == 2 ? 0 : 1, pi = t->prec == MLN_FP32 ? 1 : 0, cus = device_cus();
+  const double all = (double)g.nx * (double)g.ny, med = t->nmed / all;
+  const double bytes = t->rs * (3.0 + med * (t->comp ? 2 : 1) * t->f.D);
+  double best = 0.0;
+  int best_rows = 0;
+  for (int c = 0; c < 3; ++c) {
+    const int rows = 16 * (c + 1);
+    if (step[ni][pi][c] == 0 || 3 * K > rows + 2) continue;
+    const int64_t ox = kTmzTileX - 2 * K, oy = rows - 2 * K;
+    const double tiles = (double)((g.nx + ox - 1) / ox) * (double)((g.ny + oy - 1) / oy);
+    const double cells = tiles * rows * kTmzTileX, n = tiles / (cus * share[ni][pi][c]);
+    const double own = std::max(1.0, n) * (ends[ni][pi][c] + K * step[ni][pi][c]);
+    // (two workgroups share a compute unit at 16 rows: half of the arithmetic overlaps)
+    const double arith = cells * K * (0.15 + 0.85 * med) * cell[ni][pi] * (c == 0 ? 0.45 : 1.0);
+    const double x = 2.5 + std::max(own, (cells + all) * bytes / 4.6e6 + arith);
+    if (best_rows == 0 || x < best) {
+      best = x;
+      best_rows = rows;
+    }
+  }
+  if (us) *us = best;
+  return best_rows;
+}
+
+// Steps per launch: the least time per step.  Against one step per launch, us
+// per step on the beam of 2048 x 512 cells: three-level FP64 15.4 / 27.1,
+// compensated FP32 16.6 / 25.0, FP32 9.8 / 15.6.
+void tmz_shape(mln_tmz *t) {
+  if (t->N > 3 || t->grid.nx > (int64_t)1 << 30) return;  // one step per launch
+  double best = 0.0;
+  for (int K = 2; K <= 11; ++K) {
+    double us = 0.0;
+    const int rows = tmz_rows(t, K, &us);
+    if (rows && (best == 0.0 || us / K < best)) {
+      best = us / K;
+      t->rows = rows;
+      t->K = K;
+    }
+  }
+}
+
+// Columns a tile owns in a launch of k steps.  The Mur column needs the new E
+// of its left neighbour, one cell deeper into the halo: it must not be a
+// tile's first column.
+int tmz_columns(int64_t nx, int k) {
+  int ox = kTmzTileX - 2 * k;
+  while ((nx - 1) % ox == 0 && ox > 1) --ox;
+  return ox;
+}
+
 template <typename Real>
 int tmz_steps_typed(mln_tmz *t, const FacDev<Real> &fd, const Real (&c)[7], int64_t n) {
-  for (int64_t s = 0; s < n; ++s) {
+  const int64_t se = t->rec.snap_every;
+  for (int64_t s = 0; s < n;) {
     TmzArgs<Real> a = tmz_args<Real>(t, fd, c);
     a.n = t->step;
-    const int64_t se = t->rec.snap_every;
-    a.snap = (se > 0 && (t->step + 1) % se == 0) ? 1 : 0;
-    a.snap_i = se > 0 ? (t->step + 1) / se - 1 : 0;
+    const int k = (int)std::min<int64_t>(t->K, n - s);
     hipError_t e;
-    if constexpr (sizeof(Real) == 8)
-      e = launch_tmz<double, false>(t->N, a, t->stream);
-    else
-      e = t->comp ? launch_tmz<float, true>(t->N, a, t->stream) : launch_tmz<float, false>(t->N, a, t->stream);
+    if (k > 1) {
+      const int rows = k == t->K ? t->rows : tmz_rows(t, k, nullptr);
+      TmzTileArgs<Real> q{};
+      q.a = a;
+      q.zout = (Real *)t->z[1 - t->zcur].p;
+      q.nsteps = k;
+      q.halo = k;
+      q.ox = tmz_columns(t->grid.nx, k);
+      q.oy = rows - 2 * k;
+      q.s_snap = -1;
+      if (se > 0) {  // the first step of the launch that completes a snapshot
+        q.a.snap_i = t->step / se;
+        const int64_t f = (q.a.snap_i + 1) * se - 1 - t->step;
+        if (f < k) q.s_snap = (int)f;
+        q.gap = (int)std::min<int64_t>(se, kTmzTileMaxSteps);
+      }
+      if constexpr (sizeof(Real) == 8)
+        e = launch_tile<double, false>(t->N, rows, q, t->stream);
+      else
+        e = t->comp ? launch_tile<float, true>(t->N, rows, q, t->stream)
+                    : launch_tile<float, false>(t->N, rows, q, t->stream);
+      t->zcur = 1 - t->zcur;
+    } else {
+      a.snap = (se > 0 && (t->step + 1) % se == 0) ? 1 : 0;
+      a.snap_i = se > 0 ? (t->step + 1) / se - 1 : 0;
+      if constexpr (sizeof(Real) == 8)
+        e = launch_tmz<double, false>(t->N, a, t->stream);
+      else
+        e = t->comp ? launch_tmz<float, true>(t->N, a, t->stream) : launch_tmz<float, false>(t->N, a, t->stream);
+    }
     if (e != hipSuccess) return set_err(MLN_EHIP, std::string("TMz launch: ") + hipGetErrorString(e));
     t->cur = 1 - t->cur;
-    ++t->step;
+    t->step += k;
+    s += k;
   }
   return MLN_OK;
 }
@@ -287,7 +396,22 @@ int mln_tmz_init(const mln_medium *medium, const mln_tmz_grid *grid, const mln_t
     HIP_TRY(t->Hy[b].alloc(cells * t->rs));
   }
   const int D = t->f.D;
-  HIP_TRY(t->z.alloc((size_t)(t->comp ? 2 * D : D) * t->ld * t->rs));
+  tmz_shape(t.get());
+  const size_t zb = (size_t)(t->comp ? 2 * D : D) * t->ld * t->rs;
+  HIP_TRY(t->z[0].alloc(zb));
+  if (t->rows) {
+    const hipError_t e = t->z[1].alloc(zb);
+    if (e == hipErrorOutOfMemory) {  // no room for a second state: one step per launch, in place
+      (void)hipGetLastError();
+      t->z[1].p = nullptr;
+      t->rows = 0;
+      t->K = 1;
+    } else {
+      HIP_TRY(e);
+    }
+  }
+  rc = tmz_plan(t.get());
+  if (rc) return rc;
   rc = tmz_reset(t.get());
   if (rc) return rc;
   *out = t.release();
@@ -310,7 +434,6 @@ int mln_tmz_run(mln_tmz *t) {
 
 int mln_tmz_reset(mln_tmz *t) {
   if (!t) return set_err(MLN_EINVAL, "null handle");
-  HIP_TRY(hipStreamSynchronize(t->stream));
   return tmz_reset(t);
 }
 
