@@ -2,6 +2,7 @@
 #include <type_traits>
 
 #include "fwd_mfma.hpp"
+#include "fwd_mfma64.hpp"
 #include "fwd_wave.hpp"
 
 namespace mln {
@@ -12,16 +13,18 @@ hipError_t launch_fwd_n4(int route, bool comp, bool cf, const FwdArgs<Real> &a, 
   if (comp) {
     if constexpr (std::is_same<Real, float>::value) {
       if (route != ROUTE_ROT) return hipErrorInvalidValue;
-      if (cf)
-        hipLaunchKernelGGL((fwd_tile_kernel<4, float, ROUTE_ROT, true, true>), dim3((unsigned)nblocks), dim3(W), 0, st, a);
-      else
-        hipLaunchKernelGGL((fwd_tile_kernel<4, float, ROUTE_ROT, true>), dim3((unsigned)nblocks), dim3(W), 0, st, a);
-      return hipGetLastError();
+      return cf ? launch_mfma64<4, float, true, true>(W, a, nblocks, st)
+                : launch_mfma64<4, float, true, false>(W, a, nblocks, st);
     }
     return hipErrorInvalidValue;
   }
   switch (route) {
-    case ROUTE_ROT: hipLaunchKernelGGL((fwd_tile_kernel<4, Real, ROUTE_ROT, false>), dim3((unsigned)nblocks), dim3(W), 0, st, a); break;
+    case ROUTE_ROT:
+      if constexpr (sizeof(Real) == 8)
+        return launch_mfma64<4, double, false, false>(W, a, nblocks, st);
+      else
+        hipLaunchKernelGGL((fwd_tile_kernel<4, Real, ROUTE_ROT, false>), dim3((unsigned)nblocks), dim3(W), 0, st, a);
+      break;
     case ROUTE_DIAG: hipLaunchKernelGGL((fwd_tile_kernel<4, Real, ROUTE_DIAG, false>), dim3((unsigned)nblocks), dim3(W), 0, st, a); break;
     case ROUTE_RODR: hipLaunchKernelGGL((fwd_tile_kernel<4, Real, ROUTE_RODR, false>), dim3((unsigned)nblocks), dim3(W), 0, st, a); break;
     default: return hipErrorInvalidValue;
@@ -31,41 +34,18 @@ hipError_t launch_fwd_n4(int route, bool comp, bool cf, const FwdArgs<Real> &a, 
 
 template <typename Real>
 hipError_t launch_fwd_wave_n4(bool comp, int C, const FwdArgs<Real> &a, int64_t nblocks, hipStream_t st) {
-  switch (C) {
-    case 1:
-      if (comp) {
-        if constexpr (std::is_same<Real, float>::value)
-          hipLaunchKernelGGL((fwd_wave_kernel<4, float, true, 1>), dim3((unsigned)nblocks), dim3(64), 0, st, a);
-        else
-          return hipErrorInvalidValue;
-      } else {
-        hipLaunchKernelGGL((fwd_wave_kernel<4, Real, false, 1>), dim3((unsigned)nblocks), dim3(64), 0, st, a);
-      }
-      break;
-    case 2:
-      if (comp) {
-        if constexpr (std::is_same<Real, float>::value)
-          hipLaunchKernelGGL((fwd_wave_kernel<4, float, true, 2>), dim3((unsigned)nblocks), dim3(64), 0, st, a);
-        else
-          return hipErrorInvalidValue;
-      } else {
-        hipLaunchKernelGGL((fwd_wave_kernel<4, Real, false, 2>), dim3((unsigned)nblocks), dim3(64), 0, st, a);
-      }
-      break;
-    case 4:
-      if (comp) {
-        if constexpr (std::is_same<Real, float>::value)
-          hipLaunchKernelGGL((fwd_wave_kernel<4, float, true, 4>), dim3((unsigned)nblocks), dim3(64), 0, st, a);
-        else
-          return hipErrorInvalidValue;
-      } else {
-        hipLaunchKernelGGL((fwd_wave_kernel<4, Real, false, 4>), dim3((unsigned)nblocks), dim3(64), 0, st, a);
-      }
-      break;
-    default:
-      return hipErrorInvalidValue;
+  if (C != 1 && C != 2 && C != 4) return hipErrorInvalidValue;
+  if constexpr (std::is_same<Real, double>::value) {
+    return comp ? hipErrorInvalidValue : launch_mfma64<4, double, false, false>(64 * C, a, nblocks, st);
+  } else {
+    if (comp) return launch_mfma64<4, float, true, false>(64 * C, a, nblocks, st);
+    switch (C) {
+      case 1: hipLaunchKernelGGL((fwd_wave_kernel<4, float, false, 1>), dim3((unsigned)nblocks), dim3(64), 0, st, a); break;
+      case 2: hipLaunchKernelGGL((fwd_wave_kernel<4, float, false, 2>), dim3((unsigned)nblocks), dim3(64), 0, st, a); break;
+      case 4: hipLaunchKernelGGL((fwd_wave_kernel<4, float, false, 4>), dim3((unsigned)nblocks), dim3(64), 0, st, a); break;
+    }
+    return hipGetLastError();
   }
-  return hipGetLastError();
 }
 
 hipError_t launch_fwd_mfma_n4(int nprod, const FwdArgs<float> &a, int64_t nblocks, int W, hipStream_t st) {

@@ -2,6 +2,7 @@
 #include <type_traits>
 
 #include "fwd_mfma.hpp"
+#include "fwd_mfma64.hpp"
 #include "fwd_wave.hpp"
 
 namespace mln {
@@ -12,16 +13,18 @@ hipError_t launch_fwd_n6(int route, bool comp, bool cf, const FwdArgs<Real> &a, 
   if (comp) {
     if constexpr (std::is_same<Real, float>::value) {
       if (route != ROUTE_ROT) return hipErrorInvalidValue;
-      if (cf)
-        hipLaunchKernelGGL((fwd_tile_kernel<6, float, ROUTE_ROT, true, true>), dim3((unsigned)nblocks), dim3(W), 0, st, a);
-      else
-        hipLaunchKernelGGL((fwd_tile_kernel<6, float, ROUTE_ROT, true>), dim3((unsigned)nblocks), dim3(W), 0, st, a);
-      return hipGetLastError();
+      return cf ? launch_mfma64<6, float, true, true>(W, a, nblocks, st)
+                : launch_mfma64<6, float, true, false>(W, a, nblocks, st);
     }
     return hipErrorInvalidValue;
   }
   switch (route) {
-    case ROUTE_ROT: hipLaunchKernelGGL((fwd_tile_kernel<6, Real, ROUTE_ROT, false>), dim3((unsigned)nblocks), dim3(W), 0, st, a); break;
+    case ROUTE_ROT:
+      if constexpr (sizeof(Real) == 8)
+        return launch_mfma64<6, double, false, false>(W, a, nblocks, st);
+      else
+        hipLaunchKernelGGL((fwd_tile_kernel<6, Real, ROUTE_ROT, false>), dim3((unsigned)nblocks), dim3(W), 0, st, a);
+      break;
     case ROUTE_DIAG: hipLaunchKernelGGL((fwd_tile_kernel<6, Real, ROUTE_DIAG, false>), dim3((unsigned)nblocks), dim3(W), 0, st, a); break;
     case ROUTE_RODR: hipLaunchKernelGGL((fwd_tile_kernel<6, Real, ROUTE_RODR, false>), dim3((unsigned)nblocks), dim3(W), 0, st, a); break;
     default: return hipErrorInvalidValue;
@@ -31,21 +34,16 @@ hipError_t launch_fwd_n6(int route, bool comp, bool cf, const FwdArgs<Real> &a, 
 
 template <typename Real>
 hipError_t launch_fwd_wave_n6(bool comp, int C, const FwdArgs<Real> &a, int64_t nblocks, hipStream_t st) {
-  switch (C) {
-    case 1:
-      if (comp) {
-        if constexpr (std::is_same<Real, float>::value)
-          hipLaunchKernelGGL((fwd_wave_kernel<6, float, true, 1>), dim3((unsigned)nblocks), dim3(64), 0, st, a);
-        else
-          return hipErrorInvalidValue;
-      } else {
-        hipLaunchKernelGGL((fwd_wave_kernel<6, Real, false, 1>), dim3((unsigned)nblocks), dim3(64), 0, st, a);
-      }
-      break;
-    default:
-      return hipErrorInvalidValue;
+  if (C != 1) return hipErrorInvalidValue;
+  if constexpr (std::is_same<Real, double>::value) {
+    return comp ? hipErrorInvalidValue : launch_mfma64<6, double, false, false>(64 * C, a, nblocks, st);
+  } else {
+    if (comp) return launch_mfma64<6, float, true, false>(64 * C, a, nblocks, st);
+    switch (C) {
+      case 1: hipLaunchKernelGGL((fwd_wave_kernel<6, float, false, 1>), dim3((unsigned)nblocks), dim3(64), 0, st, a); break;
+    }
+    return hipGetLastError();
   }
-  return hipGetLastError();
 }
 
 hipError_t launch_fwd_mfma_n6(int nprod, const FwdArgs<float> &a, int64_t nblocks, int W, hipStream_t st) {

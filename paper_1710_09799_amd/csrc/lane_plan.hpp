@@ -67,4 +67,37 @@ inline LanePlan lane_plan(int N, bool fp32_plain, int state_bytes, int64_t nx, i
   return best;
 }
 
+// The same for the FP64 matrix-core kernel of N = 4, 6 (fwd_mfma64.hpp): a
+// compute unit works off its tiles in rounds of as many as its registers hold
+// (wavefronts per SIMD: two at N = 6, three at N = 4); a round costs 3 us of
+// loads and stores and K steps of L[w] us with w wavefronts on the busiest
+// SIMD, a launch F us.  Fitted to runs of 2000 to 200000 cells, us per step
+// model / measured: six levels, 50000 cells, 256 cells and 24 steps 4.2 / 4.4,
+// 128 and 30 6.4 / 6.1, 64 and 12 7.2 / 7.1; 2000 cells, 128 and 48 2.4 / 2.3;
+// four levels, 200000 cells, 128 and 12 6.1 / 6.0.
+inline LanePlan mfma64_plan(int N, int64_t nx, int cus) {
+  static const double L[2][4] = {{0.0, 1.72, 2.1, 2.3}, {0.0, 2.15, 3.65, 3.65}};
+  static const int waves[2] = {3, 2}, Ws[3] = {64, 128, 256};
+  const int ni = N == 4 ? 0 : 1;
+  const double F = N == 4 ? 3.0 : 9.0;
+  LanePlan best{256, 24};
+  double best_t = 0.0;
+  for (int W : Ws) {
+    const int share = waves[ni] * 256 / (2 * W);  // tiles a compute unit holds: W / 32 wavefronts each
+    if (share < 1) continue;
+    const int wmax = std::max(1, share * W / 128);  // wavefronts per SIMD of a full round
+    for (int K = 4; 2 * K < W && K <= 60; K += 2) {
+      const int64_t owned = W - 2 * K, tiles = (nx + owned - 1) / owned, per = (tiles + cus - 1) / cus;
+      const int64_t full = per / share, rest = per % share;
+      const double t = (F + full * (3.0 + K * L[ni][wmax]) +
+                        (rest ? 3.0 + K * L[ni][std::max<int64_t>(1, (rest * W + 127) / 128)] : 0.0)) / K;
+      if (best_t == 0.0 || t < best_t) {
+        best_t = t;
+        best = {W, K};
+      }
+    }
+  }
+  return best;
+}
+
 }  // namespace mln

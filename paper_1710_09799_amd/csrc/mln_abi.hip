@@ -334,9 +334,13 @@ int set_kernel(mln_handle *h, int variant_req, int tile, int steps_per_launch) {
   // and handles with an adjoint, whose reverse kernel overlaps the four-lane
   // launches: four lanes up to 1e5 cells, then one cell per thread.
   const bool lane = rot && h->f.N <= 3 && !h->cf && !h->adjoint;
+  // N = 4, 6 in FP64 arithmetic: the kernel on the FP64 matrix cores is behind
+  // both the workgroup and the wavefront variant; plain FP32 of N = 4 runs one
+  // wavefront per tile
+  const bool mfma64 = rot && h->f.N >= 4 && !h->mfma && (h->prec == MLN_FP64 || h->comp);
   if (variant == 0) {
     const int64_t from = lane ? lane_min_cells(h->f.N, h->prec == MLN_FP32, h->comp) : kQuadMaxAutoCells;
-    variant = !rot ? 1 : (h->f.N <= 3 ? (h->grid.nx < from ? 3 : 1) : (h->f.N == 4 && !h->cf ? 2 : 1));
+    variant = !rot ? 1 : (h->f.N <= 3 ? (h->grid.nx < from ? 3 : 1) : (h->f.N == 4 && !mfma64 ? 2 : 1));
     // the matrix-core product pays off with the compensated state at N = 3
     // and with compensated fields (measured; FP64 and plain FP32 run faster
     // on the DPP product, whose FMA chain is shorter than the MFMA latency)
@@ -402,6 +406,11 @@ int set_kernel(mln_handle *h, int variant_req, int tile, int steps_per_launch) {
   if (lane && variant == 1 && tile <= 0 && steps_per_launch <= 0) {
     const LanePlan p = lane_plan(h->f.N, h->prec == MLN_FP32, h->rs * (2 + h->f.D * (h->comp ? 2 : 1)), h->grid.nx,
                                  device_cus());
+    h->W = p.W;
+    K = p.K;
+  }
+  if (mfma64 && variant == 1 && tile <= 0 && steps_per_launch <= 0) {
+    const LanePlan p = mfma64_plan(h->f.N, h->grid.nx, device_cus());
     h->W = p.W;
     K = p.K;
   }
