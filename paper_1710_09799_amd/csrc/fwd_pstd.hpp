@@ -32,8 +32,19 @@
 //     lanes read them: per radix-4 pass its twiddles W_4h^j, j < h, and per
 //     mode pair its unpacking factor exp(-2 pi i k / nx) and half-cell shift
 //     exp(-i pi k / nx).
+// A step of one problem is a chain of ten barriers and short passes on one
+// compute unit, so the instructions between them count: from two cells per
+// thread on the grid size is a template constant, with every span, loop count
+// and LDS address, and the medium step of N = 3 keeps its factor in registers
+// (cells.hpp), two of a thread's cells at a time where both are medium.
+// Measured, us per step, half of the ring medium, before / now: N = 3, 1024
+// cells 5.0 / 3.8, 2048 cells 7.2 / 5.2, 4096 cells 13.2 / 10.0; N = 2, 2048
+// cells 5.0 / 4.0 (its three state components are served well enough by the
+// factor in LDS: 4.2 with cells.hpp).  With eight or more cells per thread
+// pairs of cells would spill (12.2 at 4096 cells).
 #pragma once
 
+#include "cells.hpp"
 #include "fwd_impl.hpp"
 
 namespace mln {
@@ -119,13 +130,17 @@ __device__ __forceinline__ double2 c_mi(double2 a) { return make_double2(a.y, -a
 // the stage of span h (twiddle W_2h^j = (W_4h^j)^2), W_L = exp(-2 pi i / L).
 // An odd stage count leaves the span-1 stage (twiddle 1) for last.  Ends
 // with a barrier.
-__device__ __forceinline__ void pstd_fft_dif(double2 *buf, const double2 *pt, int lm, int lh_first = -1) {
+//
+// LM: lm at compile time (0: not known); the passes are then unrolled, with
+// their spans, loop counts and addresses constant.  SKIP: the first pass has
+// been done (pstd_dif_first_regs).
+template <int LM, bool SKIP>
+__device__ __forceinline__ void pstd_fft_dif(double2 *buf, const double2 *pt, int lm, int T) {
   const int M = 1 << lm;
-  int lh = lh_first < 0 ? lm - 1 : lh_first;
-  for (; lh >= 1; lh -= 2) {
+  auto pass = [&](int lh) {
     const int lq = lh - 1, h = 1 << lq;
     const double2 *tw = pt + pstd_pt_off(h, lm);
-    for (int q = threadIdx.x; q < M / 4; q += blockDim.x) {
+    for (int q = threadIdx.x; q < M / 4; q += T) {
       const int j = q & (h - 1);
       const int i0 = ((q >> lq) << (lq + 2)) | j;
       const int s0 = psw(i0), s1 = psw(i0 + h), s2 = psw(i0 + 2 * h), s3 = psw(i0 + 3 * h);
@@ -140,16 +155,23 @@ __device__ __forceinline__ void pstd_fft_dif(double2 *buf, const double2 *pt, in
       buf[s2] = c_add(b2, b3);
       buf[s3] = c_mul(c_sub(b2, b3), w2);
     }
-    __syncthreads();
+    lds_barrier();
+  };
+  if constexpr (LM > 0) {
+    constexpr int first = LM - 1 - (SKIP ? 2 : 0), passes = (first + 1) / 2;
+#pragma unroll
+    for (int i = 0; i < passes; ++i) pass(first - 2 * i);
+  } else {
+    for (int lh = lm - 1 - (SKIP ? 2 : 0); lh >= 1; lh -= 2) pass(lh);
   }
-  if (lh == 0) {
-    for (int b = threadIdx.x; b < M / 2; b += blockDim.x) {
+  if (lm & 1) {
+    for (int b = threadIdx.x; b < M / 2; b += T) {
       const int s0 = psw(2 * b), s1 = psw(2 * b + 1);
       const double2 u = buf[s0], v = buf[s1];
       buf[s0] = c_add(u, v);
       buf[s1] = c_sub(u, v);
     }
-    __syncthreads();
+    lds_barrier();
   }
 }
 
@@ -159,24 +181,23 @@ __device__ __forceinline__ void pstd_fft_dif(double2 *buf, const double2 *pt, in
 // then two stages per pass (span h with twiddle conj W_2h^j, then span 2h
 // with conj W_4h^j and conj W_4h^(j+h) = i conj W_4h^j).  Ends with a
 // barrier.
-__device__ __forceinline__ void pstd_fft_dit_inv(double2 *buf, const double2 *pt, int lm, bool skip_last = false) {
+// SKIP: the last pass follows (pstd_dit_last_regs).
+template <int LM, bool SKIP>
+__device__ __forceinline__ void pstd_fft_dit_inv(double2 *buf, const double2 *pt, int lm, int T) {
   const int M = 1 << lm;
-  const int lh_end = skip_last ? lm - 2 : lm;  // passes with lh + 1 < lh_end
-  int lh = 0;
   if (lm & 1) {
-    for (int b = threadIdx.x; b < M / 2; b += blockDim.x) {
+    for (int b = threadIdx.x; b < M / 2; b += T) {
       const int s0 = psw(2 * b), s1 = psw(2 * b + 1);
       const double2 u = buf[s0], v = buf[s1];
       buf[s0] = c_add(u, v);
       buf[s1] = c_sub(u, v);
     }
-    __syncthreads();
-    lh = 1;
+    lds_barrier();
   }
-  for (; lh + 1 < lh_end; lh += 2) {
+  auto pass = [&](int lh) {
     const int h = 1 << lh;
     const double2 *tw = pt + pstd_pt_off(h, lm);
-    for (int q = threadIdx.x; q < M / 4; q += blockDim.x) {
+    for (int q = threadIdx.x; q < M / 4; q += T) {
       const int j = q & (h - 1);
       const int i0 = ((q >> lh) << (lh + 2)) | j;
       const int s0 = psw(i0), s1 = psw(i0 + h), s2 = psw(i0 + 2 * h), s3 = psw(i0 + 3 * h);
@@ -193,7 +214,14 @@ __device__ __forceinline__ void pstd_fft_dit_inv(double2 *buf, const double2 *pt
       buf[s1] = c_add(b1, q3);
       buf[s3] = c_sub(b1, q3);
     }
-    __syncthreads();
+    lds_barrier();
+  };
+  if constexpr (LM > 0) {
+    constexpr int first = LM & 1, passes = (LM - (SKIP ? 2 : 0) - first) / 2;
+#pragma unroll
+    for (int i = 0; i < passes; ++i) pass(first + 2 * i);
+  } else {
+    for (int lh = lm & 1; lh + 1 < lm - (SKIP ? 2 : 0); lh += 2) pass(lh);
   }
 }
 
@@ -301,22 +329,35 @@ template <int N, int C, int TMAX>
 __global__ void __launch_bounds__(TMAX) fwd_pstd_kernel(PstdArgs a) {
   constexpr int D = N * N - 1;
   constexpr int R = (C + 3) / 4;  // mode pairs per thread: (M / 2) / T rounded up
+  // the medium step of N = 2, 3: cells.hpp, the factor in registers
+  constexpr bool CELLS = N == 3;
   using L = RotLds<N, double, false>;
   extern __shared__ double2 pstd_lds[];
-  __shared__ double sF[L::size];
-  __shared__ double sP[N * D + N];
-  const int lm = a.log2m, M = 1 << lm;
+  __shared__ double sF[CELLS ? 1 : L::size];
+  __shared__ double sP[CELLS ? 1 : N * D + N];
+  // from two cells per thread on the grid is C TMAX cells: every span, loop
+  // count and address of the transforms is known at compile time
+  constexpr int LM = C == 1 ? 0 : __builtin_ctz(C * TMAX / 2);
+  const int lm = C == 1 ? a.log2m : LM, M = 1 << lm;
   double2 *buf = pstd_lds;            // M packed elements, swizzled
   double *bufd = reinterpret_cast<double *>(buf);
   double2 *pt = pstd_lds + M;         // pass twiddles
   double2 *mw = pt + a.pt_size;       // per mode pair: exp(-2 pi i k / nx)
   double2 *me = mw + M / 2;           //                exp(-i pi k / nx)
   const PstdInst in = a.inst[blockIdx.x];
-  const int T = blockDim.x, t = threadIdx.x;
+  const int T = C == 1 ? (int)blockDim.x : TMAX, t = threadIdx.x;
   const int64_t nx = a.nx, nmed = a.me - a.mb;
 
-  L::stage(in.fac, sF);
-  L::stage_pop(in.fac, sP);
+  constexpr int NC = CELLS ? N : 2;
+  CellFac<NC, double> F;
+  CellK<NC, double> K;
+  if constexpr (CELLS) {
+    F.set(in.fac);
+    K.load(F);
+  } else {
+    L::stage(in.fac, sF);
+    L::stage_pop(in.fac, sP);
+  }
   for (int i = t; i < a.pt_size + M; i += T) pt[i] = a.tab[i];
 
   double E[C];
@@ -327,12 +368,15 @@ __global__ void __launch_bounds__(TMAX) fwd_pstd_kernel(PstdArgs a) {
   // components per thread: N = 2 with 4 or 8 cells, N = 3 with 4)
   constexpr bool REG = C % 4 == 0 && D * C <= 32;
   constexpr int CR = REG ? C : 1;
+  int medium = 0, wave_med = 0;  // bit c: the thread's cell c, a cell c of the wavefront in the medium
   double Hc[CR];  // with REG: H of the thread's cells (at entry and at exit)
 #pragma unroll
   for (int c = 0; c < C; ++c) {
     const int64_t i = t + (int64_t)c * T;
     E[c] = in.E[i];
     const bool med = i >= a.mb && i < a.me;
+    medium |= med << c;
+    wave_med |= wave_any(med) << c;
 #pragma unroll
     for (int j = 0; j < D; ++j) z[c][j] = med ? in.z[j * a.ld + (i - a.mb)] : 0.0;
     if constexpr (REG)
@@ -340,16 +384,17 @@ __global__ void __launch_bounds__(TMAX) fwd_pstd_kernel(PstdArgs a) {
     else
       bufd[pstd_real_slot(i)] = in.H[i];
   }
+  wave_med = __builtin_amdgcn_readfirstlane(wave_med);
   __syncthreads();  // also orders the tables
   if constexpr (REG) {
     pstd_dif_first_regs<C>(bufd, pt, lm, T, t, Hc);
-    __syncthreads();
+    lds_barrier();
   }
 
   // H into Fourier space: modes k and M - k of the pairs this thread owns;
   // the k = 0 slot (DC and Nyquist modes, which no update touches) is kept
   // as packed for the way back.
-  pstd_fft_dif(buf, pt, lm, REG ? lm - 3 : -1);
+  pstd_fft_dif<LM, REG>(buf, pt, lm, T);
   double2 hk[R], hm[R];
   double2 h0 = make_double2(0.0, 0.0);
 #pragma unroll
@@ -362,7 +407,7 @@ __global__ void __launch_bounds__(TMAX) fwd_pstd_kernel(PstdArgs a) {
     }
   }
   if (t == 0) h0 = buf[0];
-  __syncthreads();
+  lds_barrier();
 
   int64_t snap_next = a.snap_next, si = a.snap_i0;
   for (int s = 0; s < a.nsteps; ++s) {
@@ -376,8 +421,8 @@ __global__ void __launch_bounds__(TMAX) fwd_pstd_kernel(PstdArgs a) {
 #pragma unroll
       for (int c = 0; c < C; ++c) bufd[pstd_real_slot(ts + c * T)] = E[c];
     }
-    __syncthreads();
-    pstd_fft_dif(buf, pt, lm, REG ? lm - 3 : -1);
+    lds_barrier();
+    pstd_fft_dif<LM, REG>(buf, pt, lm, T);
     // Mode-wise: H += (dt / mu) i kappa e^{+i kappa dx / 2} F(E^n); then the
     // packed spectrum of (cb / M) D- H for the inverse transform.  With
     // e = exp(-i pi k / nx): e^{+i kappa_k dx / 2} = conj e and
@@ -404,25 +449,84 @@ __global__ void __launch_bounds__(TMAX) fwd_pstd_kernel(PstdArgs a) {
       }
     }
     if (t == 0) buf[0] = make_double2(0.0, 0.0);
-    __syncthreads();
-    pstd_fft_dit_inv(buf, pt, lm, REG);
+    lds_barrier();
+    pstd_fft_dit_inv<LM, REG>(buf, pt, lm, T);
     double Dh[CR];  // with REG: (cb / M) D- H of the thread's cells
     if constexpr (REG) pstd_dit_last_regs<C>(buf, pt, lm, T, ts, Dh);
+    double P[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) P[c] = 0.0;
+    if constexpr (CELLS) {
+      // cells c .. c + G - 1 of the thread, all lanes; those beside the medium
+      // keep no state
+      auto cells = [&](auto first, auto count) {
+        constexpr int c0 = decltype(first)::value, G = decltype(count)::value;
+        double e[G], y[G][D], p[G];
+#pragma unroll
+        for (int c = 0; c < G; ++c) {
+          e[c] = E[c0 + c];
+#pragma unroll
+          for (int j = 0; j < D; ++j) y[c][j] = z[c0 + c][j];
+        }
+        cells_rotate<N, double, G>(F, e, y);
+        if (snap && in.pop_out) {
+#pragma unroll
+          for (int c = 0; c < G; ++c) {
+            const int64_t i = ts + (int64_t)(c0 + c) * T;
+            if (i >= a.mb && i < a.me)
+              cells_record<N, double>(in.fac.pop, in.fac.popc, y[c], in.pop_out + si * N * nmed + (i - a.mb), nmed);
+          }
+        }
+        cells_shared<N, double, false, G>(F, K, y, p);
+#pragma unroll
+        for (int c = 0; c < G; ++c) {
+          const bool med = (medium >> (c0 + c)) & 1;
+          P[c0 + c] = med ? p[c] : 0.0;
+#pragma unroll
+          for (int j = 0; j < D; ++j) z[c0 + c][j] = med ? y[c][j] : 0.0;
+        }
+      };
+      bool done = false;  // uniform
+      auto run = [&](auto self, auto ic) {
+        constexpr int c = decltype(ic)::value;
+        if constexpr (c < C) {
+          if (done) {
+            done = false;
+          } else if ((wave_med >> c) & 1) {
+            if constexpr (c + 1 < C && C <= 4) {
+              if ((wave_med >> (c + 1)) & 1) {
+                cells(std::integral_constant<int, c>(), std::integral_constant<int, 2>());
+                done = true;
+              } else {
+                cells(std::integral_constant<int, c>(), std::integral_constant<int, 1>());
+              }
+            } else {
+              cells(std::integral_constant<int, c>(), std::integral_constant<int, 1>());
+            }
+          }
+          self(self, std::integral_constant<int, c + 1>());
+        }
+      };
+      run(run, std::integral_constant<int, 0>());
+    } else {
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        const int64_t i = ts + (int64_t)c * T;
+        if (i >= a.mb && i < a.me) {
+          double *pp = (snap && in.pop_out) ? in.pop_out + si * N * nmed + (i - a.mb) : nullptr;
+          P[c] = cell_step<N, double, ROUTE_ROT, false>(in.fac, sF, sP, E[c], z[c], zl, pp, nmed, a.opaque0 * s);
+        }
+      }
+    }
 #pragma unroll
     for (int c = 0; c < C; ++c) {
       const int64_t i = ts + (int64_t)c * T;
-      double P = 0.0;
-      if (i >= a.mb && i < a.me) {
-        const int64_t cm = i - a.mb;
-        double *pp = (snap && in.pop_out) ? in.pop_out + si * N * nmed + cm : nullptr;
-        P = cell_step<N, double, ROUTE_ROT, false>(in.fac, sF, sP, E[c], z[c], zl, pp, nmed, a.opaque0 * s);
-      }
       double dh;
       if constexpr (REG)
         dh = Dh[c];
       else
         dh = bufd[pstd_real_slot(i)];
-      E[c] = a.ca * E[c] - a.cb * P + dh;
+      E[c] = a.ca * E[c] - a.cb * P[c] + dh;
       if (i == nx - 1 && in.probe) in.probe[n + 1] = E[c];
       if (snap && in.e_out) in.e_out[si * nx + i] = E[c];
     }
@@ -437,7 +541,7 @@ __global__ void __launch_bounds__(TMAX) fwd_pstd_kernel(PstdArgs a) {
   }
 
   // H back to real space (after every thread has read its last D- H)
-  __syncthreads();
+  lds_barrier();
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int u = t + r * T;
@@ -450,8 +554,8 @@ __global__ void __launch_bounds__(TMAX) fwd_pstd_kernel(PstdArgs a) {
     }
   }
   if (t == 0) buf[0] = h0;
-  __syncthreads();
-  pstd_fft_dit_inv(buf, pt, lm, REG);
+  lds_barrier();
+  pstd_fft_dit_inv<LM, REG>(buf, pt, lm, T);
   if constexpr (REG) pstd_dit_last_regs<C>(buf, pt, lm, T, t, Hc);
   const double inv_m = 1.0 / (double)M;
   // a fresh copy of the thread index, so that the write-back addresses are

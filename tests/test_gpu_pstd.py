@@ -220,3 +220,18 @@ def test_pstd_empty_medium_matches_oracle(orc):
     assert out["pop"] is None or out["pop"].size == 0
     ref["pop"] = None
     _check(out, ref, h_final=out["h"])
+
+
+@pytest.mark.parametrize("nx,med,tmax", [(64, (1, 63), 256), (1024, (1, 1023), 512), (1024, (30, 700), 256),
+                                         (2048, (300, 1900), 512), (2048, (600, 1500), 512), (2048, (5, 2040), 256)])
+def test_pstd_medium_over_several_cells_of_a_thread(orc, nx, med, tmax):
+    """Media over one, two, three and all cells of a thread, with edges inside
+    a wavefront."""
+    p, e0, h0 = W.pstd_random(3, 21, nx=nx, nt=12, med=med)
+    print(f"[case] pstd cells nx={nx} med={med} threads<={tmax}", flush=True)
+    ref = orc.pstd_run(p, snap_every=4, e_init=e0, h_init=h0)
+    s = mln.Pstd([p], e_init=e0, h_init=h0, snap_every=4, steps_per_launch=5, max_threads=tmax)
+    out = {k: (v.cpu().numpy() if v is not None else None) for k, v in s.run()[0].items()}
+    e, h = s.fields(0)
+    s.close()
+    _check(out, ref, h_final=h)
