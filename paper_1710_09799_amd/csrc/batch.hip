@@ -173,6 +173,9 @@ int configure(mln_batch *b, int variant, int W, int K) {
     h->halo = K;
     set_owned(h);
   }
+  int k = K;  // all problems take the same launches
+  for (mln_handle *h : b->inst) k = std::min(k, h->halo);
+  if (k < K) return configure(b, variant, W, k);
   b->variant = variant;
   b->W = W;
   b->halo = K;

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -129,14 +130,32 @@ struct mln_handle {
 
 namespace mln {
 
+// The largest number of owned cells up to `owned` of which x is no multiple
+// (0: none from half of it on); a multiple of 4 or 2 where `owned` is one and
+// that costs little (it keeps the runs of cells per lane whole).
+inline int no_multiple(int64_t x, int owned) {
+  if (x <= 0) return owned;
+  for (int unit : {4, 2, 1}) {
+    if (owned % unit) continue;
+    const int least = unit > 1 ? owned - owned / 4 : (owned + 1) / 2;
+    for (int d = owned; d >= std::max(2, least); d -= unit)
+      if (x % d) return d;
+  }
+  return 0;
+}
+
 // Owned cells of the tiles and their number for tiles of h->W cells and
 // h->halo steps per launch.  The last cell (Mur) needs the new E of its left
 // neighbour, one cell deeper into the halo than the others, so it must not be
-// a tile's first owned cell.
+// a tile's first owned cell; where a tile owns so few cells that none of their
+// numbers will do, fewer steps per launch make room.
 inline void set_owned(mln_handle *h) {
-  h->owned = h->W - 2 * h->halo;
-  const int unit = h->owned % 4 == 0 ? 4 : (h->owned % 2 == 0 ? 2 : 1);  // keeps the runs of cells per lane whole
-  while ((h->grid.nx - 1) % h->owned == 0 && h->owned > 1) h->owned = h->owned > unit ? h->owned - unit : h->owned - 1;
+  for (;;) {
+    h->owned = no_multiple(h->grid.nx - 1, h->W - 2 * h->halo);
+    if (h->owned || h->halo == 1) break;
+    --h->halo;
+  }
+  if (!h->owned) h->owned = h->W - 2 * h->halo;
   h->ntiles = (h->grid.nx + h->owned - 1) / h->owned;
 }
 

@@ -1270,7 +1270,12 @@ int mln_grad(mln_handle *h, const double *dJ_dprobe, mln_grads *out) {
   }
   // backwards the last cell (Mur) reaches two cells to its left in a step, so
   // it must not be the first cell beyond a tile
-  while (h->grid.nx - 1 > rhalo && (h->grid.nx - 1 - rhalo) % rowned == 0 && rowned > 1) --rowned;
+  for (;;) {
+    const int d = no_multiple(h->grid.nx - 1 - rhalo, rW - 2 * rhalo);
+    rowned = d ? d : rW - 2 * rhalo;
+    if (d || rhalo == 1) break;
+    --rhalo;
+  }
   rtiles = (h->grid.nx + rowned - 1) / rowned;
   if (!h->gprobe.p) {
     for (int b = 0; b < 2; ++b) {

@@ -131,3 +131,19 @@ def test_adjoint_last_cell_beyond_a_tile(orc, variant, tile, k):
         for q in ref:
             dev = np.max(np.abs(np.asarray(g[q]) - np.asarray(ref[q]))) / np.max(np.abs(ref[q]))
             assert dev < 1e-9, (nx, q, dev)
+
+
+@pytest.mark.parametrize("nx", [97, 121, 61])
+def test_last_cell_and_small_owned_parts(orc, nx):
+    """nx - 1 a multiple of many numbers of owned cells, down to two of them."""
+    p = W.random_problem(3, 5, nx=nx, nt=200)
+    ref = orc.run(p, snap_every=50)
+    for variant, tile, k in (("quad", 32, 8), ("quad", 32, 10), ("quad", 32, 15), ("block", 64, 26), ("block", 64, 31)):
+        got = mln.run(p, snap_every=50, variant=variant, tile=tile, steps_per_launch=k)
+        ee, ep = _errs(got, ref)
+        assert ee < 1e-12 and ep < 1e-12, (variant, tile, k, ee, ep)
+    b = mln.Batch([p, W.random_problem(3, 6, nx=nx + 1, nt=200)], precision="fp64", snap_every=50, variant="quad",
+                  tile=32, steps_per_launch=15)
+    ee, ep = _errs({q: v.cpu().numpy() for q, v in b.run()[0].items()}, ref)
+    b.close()
+    assert ee < 1e-12 and ep < 1e-12, (ee, ep)
