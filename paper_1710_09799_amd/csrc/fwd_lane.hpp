@@ -169,7 +169,7 @@ __device__ __forceinline__ void lane_tile(const FwdArgs<Real> &a, ColdArgs<Real>
 #pragma unroll
       for (int j = 0; j < C; ++j) Em[j] = (M)E[j];
       cells_rotate<N, M, C>(F, Em, z);
-      if (snap) {
+      if (__builtin_expect(snap, 0)) {
         const ColdArgs<Real> c = cold_again<Real>(cold);
         const int64_t nmed = c->me - c->mb;
         double *pop = c->pop_out;
@@ -218,7 +218,7 @@ __device__ __forceinline__ void lane_tile(const FwdArgs<Real> &a, ColdArgs<Real>
             c->probe_out[step0 + s + 1] = (double)E[j];
         }
     }
-    if (snap) {
+    if (__builtin_expect(snap, 0)) {
       const ColdArgs<Real> c = cold_again<Real>(cold);
       if (c->e_out) {
 #pragma unroll

@@ -298,7 +298,7 @@ __global__ void __launch_bounds__(4 * kMaxMfma64Tile / C) fwd_mfma64_kernel(FwdA
           }
         }
       }
-      if (snap) {
+      if (__builtin_expect(snap, 0)) {
         const ColdArgs<Real> c = cold_again<Real>(cold);
         double *pop = c->pop_out;
         if (pop) {
@@ -380,7 +380,7 @@ __global__ void __launch_bounds__(4 * kMaxMfma64Tile / C) fwd_mfma64_kernel(FwdA
 #pragma unroll
       for (int q = 0; q < C; ++q) sE[(s & 1) ^ 1][ce + 16 * q] = E[q];
     }
-    if (snap) {
+    if (__builtin_expect(snap, 0)) {
       const ColdArgs<Real> c = cold_again<Real>(cold);
       if (c->e_out && g == 0) {
 #pragma unroll

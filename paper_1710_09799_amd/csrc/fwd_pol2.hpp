@@ -535,7 +535,7 @@ pol2_gather<NJ>(t0, t1, u);
         x1 = w1 + (cy * w1 - sy * w0);
         Pz = p0z + quad_sum(wz0 * x0 + wz1 * x1);
         Py = p0y + quad_sum(wy0 * x0 + wy1 * x1);
-        if (snap && own && a.pop_out) {
+        if (__builtin_expect(snap, 0)) if (own && a.pop_out) {
 #pragma unroll
           for (int lv = 0; lv < N; ++lv) {
             const double pr = (r0 < D ? sP[lv * D + r0] * x0 : 0.0) + (r1 < D ? sP[lv * D + r1] * x1 : 0.0);
@@ -561,7 +561,7 @@ pol2_gather<NJ>(x0, x1, u);
         sH[b ^ 1][1][q] = hy.Hr;
         sE[b ^ 1][0][q] = Ezn;
         sE[b ^ 1][1][q] = Eyn;
-        if (snap && own) {
+        if (__builtin_expect(snap, 0)) if (own) {
           if (a.ez_out) a.ez_out[si * nx + g] = Ezn;
           if (a.ey_out) a.ey_out[si * nx + g] = Eyn;
         }
@@ -572,7 +572,7 @@ pol2_gather<NJ>(x0, x1, u);
           if (last) {
             if (a.probe_z) a.probe_z[n + 1] = Ebz;
             if (a.probe_y) a.probe_y[n + 1] = Eby;
-            if (snap) {
+            if (__builtin_expect(snap, 0)) {
               if (a.ez_out) a.ez_out[si * nx + nx - 1] = Ebz;
               if (a.ey_out) a.ey_out[si * nx + nx - 1] = Eby;
             }
@@ -582,7 +582,7 @@ pol2_gather<NJ>(x0, x1, u);
     }
     __syncthreads();
     b ^= 1;
-    if (snap) {
+    if (__builtin_expect(snap, 0)) {
       sn += a.snap_every;
       ++si;
     }

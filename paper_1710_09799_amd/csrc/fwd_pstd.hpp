@@ -469,7 +469,7 @@ __global__ void __launch_bounds__(TMAX) fwd_pstd_kernel(PstdArgs a) {
           for (int j = 0; j < D; ++j) y[c][j] = z[c0 + c][j];
         }
         cells_rotate<N, double, G>(F, e, y);
-        if (snap && in.pop_out) {
+        if (__builtin_expect(snap, 0) && in.pop_out) {
 #pragma unroll
           for (int c = 0; c < G; ++c) {
             const int64_t i = ts + (int64_t)(c0 + c) * T;
@@ -530,7 +530,7 @@ __global__ void __launch_bounds__(TMAX) fwd_pstd_kernel(PstdArgs a) {
       if (i == nx - 1 && in.probe) in.probe[n + 1] = E[c];
       if (snap && in.e_out) in.e_out[si * nx + i] = E[c];
     }
-    if (snap) {
+    if (__builtin_expect(snap, 0)) {
       snap_next += a.snap_every;
       ++si;
     }

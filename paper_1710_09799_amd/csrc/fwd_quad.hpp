@@ -138,14 +138,10 @@ __device__ __forceinline__ void quad_tile(const FwdArgs<Real> &a, int64_t tile) 
   // exchanged E of cell c at index c + 1; indices 0 and W + 1 stay zero
   __shared__ Real sE[2][kMaxQuadTile + 2], sEl[2][CF ? kMaxQuadTile + 2 : 1];
   __shared__ Real sSrc[kMaxStepsPerLaunch], sSrcl[CF ? kMaxStepsPerLaunch : 1];
-  __shared__ Real sMur, sMurl;
-  // Single-precision three-level kernels keep the probe values of a launch
-  // in LDS and store them after the step loop: a global store in the loop
-  // makes the next step wait for its completion there (measured: 4-9 %
-  // faster).  The other instantiations run as fast or faster with the store
-  // in the loop and keep it.
-  constexpr bool kProbeLds = N == 3 && std::is_same<Real, float>::value && !CF;
-  __shared__ Real sPr[kProbeLds ? kMaxStepsPerLaunch : 1];
+  // The probe values of a launch wait in LDS and are stored after the step
+  // loop: a global store in the loop makes the next step wait for its
+  // completion there, in the tile that every launch waits for.
+  __shared__ double sPr[kMaxStepsPerLaunch];
   const int t = threadIdx.x;
   // state components 2r, 2r+1 of cell cl; DPP form: lane 4 cl + r; matrix-
   // core form: wavefront cl / 16, lane 16 r + (cl mod 16)
@@ -159,6 +155,14 @@ __device__ __forceinline__ void quad_tile(const FwdArgs<Real> &a, int64_t tile) 
   const bool tile_med = (base < a.me) && (base + W > a.mb);
   const bool has_right = (base <= a.nx - 1) && (base + W > a.nx - 1);
   const bool owned = in_dom && cl >= a.halo && cl < a.halo + a.owned;
+  // The boundary cell nx-1 belongs to the lanes of cell nx-2, which hold what
+  // its update needs: E^{n+1}_{nx-1} = E^n_{nx-2} + kmur (E^{n+1}_{nx-2} -
+  // E^n_{nx-1}).  Passed from lane to lane through LDS instead it costs the
+  // tile a second barrier per step, and every launch waits for that tile (us
+  // per step, 4000 cells of medium, three levels: FP64 0.65 with it, 0.58
+  // without, FP32 0.50 / 0.45, two-float fields 0.72 / 0.64).
+  const bool mur = g == a.nx - 2;
+  const bool mur_owned = mur && cl + 1 >= a.halo && cl + 1 < a.halo + a.owned;
   const int64_t c = g - a.mb;
   const int64_t nmed = a.me - a.mb;
   const int i0 = 2 * r, i1 = 2 * r + 1;
@@ -208,9 +212,12 @@ __device__ __forceinline__ void quad_tile(const FwdArgs<Real> &a, int64_t tile) 
   // E, H and the private copy Hl of the face left of the cell; with CF each
   // has a low part (Elo, Hlo, Hll)
   Real E = 0, H = 0, Hl = 0, Elo = 0, Hlo = 0, Hll = 0;
+  Real Eb = 0, Ebl = 0;  // mur: E of the boundary cell
   Real y0 = 0, y1 = 0, l0 = 0, l1 = 0;
   if (in_dom) {
     E = a.Ein[g];
+    if (mur) Eb = a.Ein[g + 1];
+    if (CF && mur) Ebl = a.Ein[a.nx + g + 1];
     if (g <= a.nx - 2) H = a.Hin[g];
     if (g >= 1) Hl = a.Hin[g - 1];
     if constexpr (CF) {
@@ -239,6 +246,11 @@ __device__ __forceinline__ void quad_tile(const FwdArgs<Real> &a, int64_t tile) 
     if constexpr (CF) sEl[b][i] = Real(0);
   }
   __syncthreads();
+  // what a recording step or the tape needs is marked unlikely: laid out
+  // between the blocks of the common step it costs that step instruction
+  // fetches (us per step, FP64: two levels, 2000 cells 0.48 with it inside,
+  // 0.45 apart; three levels, 20000 cells 0.76 / 0.72, compensated FP32 0.64 /
+  // 0.60);
   // the step loop keeps its bookkeeping in 32-bit scalars and its field
   // updates free of divergent branches (the step's time is the length of
   // one wavefront's instruction stream): the next snapshot as a step index
@@ -270,12 +282,14 @@ __device__ __forceinline__ void quad_tile(const FwdArgs<Real> &a, int64_t tile) 
     sE[b][cl + 1] = E;
     if constexpr (CF) sEl[b][cl + 1] = Elo;
     lds_barrier();
-    const Real El = sE[b][cl], Er = sE[b][cl + 2];
+    const Real El = sE[b][cl], Ex = sE[b][cl + 2];
+    const Real Er = mur ? Eb : Ex;
     const Real src = sSrc[s];
     Real Ell = 0, Erl = 0, srcl = 0;
     if constexpr (CF) {
       Ell = sEl[b][cl];
-      Erl = sEl[b][cl + 2];
+      const Real Exl = sEl[b][cl + 2];
+      Erl = mur ? Ebl : Exl;
       srcl = sSrcl[s];
     }
     // H at both faces of the cell; the private copy Hl is updated with the
@@ -297,7 +311,7 @@ __device__ __forceinline__ void quad_tile(const FwdArgs<Real> &a, int64_t tile) 
       // cell's own role (is_med, owned) only selects what is kept
       if (tile_med) {
         mf_apply();
-        if (a.tape) {
+        if (__builtin_expect(a.tape != nullptr, 0)) {
           const int64_t n = a.step0 + s;
           if (owned && is_med && n >= a.tape_step0) {
             Real *tp = a.tape + (n - a.tape_step0) * (D + 1) * a.ld + c;
@@ -314,7 +328,7 @@ __device__ __forceinline__ void quad_tile(const FwdArgs<Real> &a, int64_t tile) 
         const Real d0 = (cm * y0 + sn * y1) + (cm * zr0 + sn * zr1);
         const Real d1 = (cm * y1 - sn * y0) + (cm * zr1 - sn * zr0);
         const Real u0 = y0 + d0, u1 = y1 + d1;
-        if (snap && a.pop_out) {
+        if (__builtin_expect(snap, 0) && a.pop_out) {
           // population of level lv = popc + pop row lv . y'' (FP64): each
           // lane's two terms, summed over the cell's four lanes
           Real e0 = 0, e1 = 0;
@@ -345,7 +359,7 @@ __device__ __forceinline__ void quad_tile(const FwdArgs<Real> &a, int64_t tile) 
     } else if (tile_med && is_med) {
       // (the DPP kernel keeps the per-cell branch: measured faster here
       // than the branch-free form the matrix-core kernel uses)
-      if (a.tape) {
+      if (__builtin_expect(a.tape != nullptr, 0)) {
         const int64_t n = a.step0 + s;
         if (owned && n >= a.tape_step0) {
           Real *tp = a.tape + (n - a.tape_step0) * (D + 1) * a.ld + c;
@@ -376,7 +390,7 @@ __device__ __forceinline__ void quad_tile(const FwdArgs<Real> &a, int64_t tile) 
       zz[5] = quad_bcast<2>(u1);
       zz[6] = quad_bcast<3>(u0);
       zz[7] = quad_bcast<3>(u1);
-      if (snap && owned && is_med && a.pop_out) {
+      if (__builtin_expect(snap, 0)) if (a.pop_out && owned) {
         // all four lanes take part in the broadcasts; lanes 0..N-1 each
         // form the population of one level.  With COMP the low parts of
         // y'' are l + the rounding error of y + d (two-sum).
@@ -435,29 +449,22 @@ __device__ __forceinline__ void quad_tile(const FwdArgs<Real> &a, int64_t tile) 
       E = interior ? En : (is_src ? src : E);
       if constexpr (CF) Elo = interior ? Enl : (is_src ? srcl : Elo);
     }
-    if (has_right) {  // first-order Mur boundary at cell nx-1
-      if (g == a.nx - 2 && r == 0) {
-        sMur = E;
-        sMurl = Elo;
+    if (has_right) {  // first-order Mur boundary at cell nx-1 (kept by the lanes of cell nx-2 only)
+      if constexpr (CF) {
+        Real eb = Eold, ebl = Eoldl;
+        add_comp(eb, ebl, a.kmur * ((E - Eb) + (Elo - Ebl)));
+        Eb = eb;
+        Ebl = ebl;
+      } else {
+        Eb = Eold + a.kmur * (E - Eb);
       }
-      lds_barrier();
-      if (g == a.nx - 1) {
-        if constexpr (CF) {
-          E = El;
-          Elo = Ell;
-          add_comp(E, Elo, a.kmur * ((sMur - Eold) + (sMurl - Eoldl)));
-        } else {
-          E = El + a.kmur * (sMur - Eold);
-        }
-        if constexpr (kProbeLds) {
-          if (owned && r == 0) sPr[s] = E;
-        } else {
-          if (a.probe_out && owned && r == 0) a.probe_out[a.step0 + s + 1] = (double)E + (double)Elo;
-        }
-      }
+      if (mur && r == 0) sPr[s] = (double)Eb + (double)Ebl;
     }
-    if (snap) {
-      if (owned && r == 0 && a.e_out) a.e_out[si * a.nx + g] = (double)E + (double)Elo;
+    if (__builtin_expect(snap, 0)) {
+      if (r == 0 && a.e_out) {
+        if (owned && g != a.nx - 1) a.e_out[si * a.nx + g] = (double)E + (double)Elo;
+        if (mur_owned) a.e_out[si * a.nx + g + 1] = (double)Eb + (double)Ebl;
+      }
       s_snap += snap_gap;
       ++si;
     }
@@ -465,11 +472,16 @@ __device__ __forceinline__ void quad_tile(const FwdArgs<Real> &a, int64_t tile) 
   if constexpr (MF) {
     if (tile_med) mf_apply();
   }
-  if constexpr (kProbeLds) {
-    if (a.probe_out && has_right && owned && r == 0 && g == a.nx - 1)
-      for (int s = 0; s < a.nsteps; ++s) a.probe_out[a.step0 + 1 + s] = (double)sPr[s];
+  if (mur_owned && r == 0) {
+    a.Eout[g + 1] = Eb;
+    if constexpr (CF) a.Eout[a.nx + g + 1] = Ebl;
   }
-  if (owned) {
+  // (the tile that owns the boundary cell: uniform)
+  if (a.probe_out && a.nx - 1 - base >= a.halo && a.nx - 1 - base < a.halo + a.owned) {
+    lds_barrier();
+    for (int s = threadIdx.x; s < a.nsteps; s += blockDim.x) a.probe_out[a.step0 + 1 + s] = sPr[s];
+  }
+  if (owned && g != a.nx - 1) {
     if (r == 0) {
       a.Eout[g] = E;
       if (g <= a.nx - 2) a.Hout[g] = H;

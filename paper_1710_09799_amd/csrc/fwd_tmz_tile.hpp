@@ -174,7 +174,7 @@ __global__ void __launch_bounds__(64 * NW) fwd_tmz_tile_kernel(TmzTileArgs<Real>
           for (int k = 0; k < D; ++k) y[c][k] = z[q + c][k];
         }
         cells_rotate<N, M, G>(F, e, y);
-        if (snap) {
+        if (__builtin_expect(snap, 0)) {
           const TmzCold<Real> cq = tmz_again<Real>(cold);
           double *pop = cq->a.pop_out;
           const int rows = (int)cq->a.my1 - (int)cq->a.my0, cols = (int)cq->a.mx1 - (int)cq->a.mx0;
@@ -242,7 +242,7 @@ __global__ void __launch_bounds__(64 * NW) fwd_tmz_tile_kernel(TmzTileArgs<Real>
         E[c] = v;
       }
     }
-    if (snap) {
+    if (__builtin_expect(snap, 0)) {
       const TmzCold<Real> cq = tmz_again<Real>(cold);
       if (cq->a.e_out) {
         double *e = cq->a.e_out + (cq->a.snap_i + snaps) * cq->a.nx * cq->a.ny + i;

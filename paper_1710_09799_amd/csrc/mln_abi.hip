@@ -386,16 +386,17 @@ int set_kernel(mln_handle *h, int variant_req, int tile, int steps_per_launch) {
     // tiles up to about one per compute unit, and every launch has a fixed
     // cost (prologue, epilogue, kernel boundary), so take the largest step
     // count that keeps the tiles within the compute units.  Matrix-core
-    // forms: even counts up to 24 at N = 3, 30 at N = 4, 6, tiles up to the
-    // unit count; DPP form: up to 56, tiles up to 9/10 of the units (on
-    // 20000 cells 20 steps and 228 tiles beat 24 steps and 250 tiles by 7 %;
-    // on 2000 cells 56 steps run 1.3x faster than 16).  Larger grids keep
-    // the fixed default above.
+    // forms: even counts up to 56 at N = 3 (compensated FP32, 4000 cells:
+    // 0.55 us per step with 56, 0.62 with 24; 20000 cells take 24), 30 at N =
+    // 4, 6, tiles up to the unit count; DPP form: up to 56, tiles up to 9/10
+    // of the units (on 20000 cells 20 steps and 228 tiles beat 24 steps and
+    // 250 tiles by 7 %; on 2000 cells 56 steps run 1.3x faster than 16).
+    // Larger grids keep the fixed default above.
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || cus <= 0)
       cus = 256;
     const bool mf = h->qmf || h->mfma;
-    const int kmax = std::min(mf ? (h->qmf ? 24 : 30) : 56, (h->W - 1) / 2);
+    const int kmax = std::min(h->mfma ? 30 : 56, (h->W - 1) / 2);
     const int64_t maxtiles = mf ? cus : cus * 9 / 10;
     for (int k = mf ? kmax & ~1 : kmax; k >= 8; k -= mf ? 2 : 1)
       if ((h->grid.nx + (h->W - 2 * k) - 1) / (h->W - 2 * k) <= maxtiles) {
@@ -1247,9 +1248,7 @@ int mln_grad(mln_handle *h, const double *dJ_dprobe, mln_grads *out) {
     rowned = rW - 2 * rhalo;
     rtiles = (h->grid.nx + rowned - 1) / rowned;
   } else if (rquad && !(f64 && N == 3)) {
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || cus <= 0)
-      cus = 256;
+    const int cus = device_cus();
     rW = kMaxAdjQuadTile;
     rhalo = 16;
     for (int k = 48; k > 16; k -= 2)
@@ -1261,10 +1260,18 @@ int mln_grad(mln_handle *h, const double *dJ_dprobe, mln_grads *out) {
     rtiles = (h->grid.nx + rowned - 1) / rowned;
   } else if (rquad && f64 && N == 3 && rW > 64) {
     // the FP64 three-level reverse step runs spill-free only on the
-    // 256-lane build: 64-cell tiles, 16 steps per launch (the tape is read
-    // by cell, so the reverse tiling need not be the forward one)
+    // 256-lane build: 64-cell tiles (the tape is read by cell, so the reverse
+    // tiling need not be the forward one) and the largest even step count up
+    // to 24 that keeps the tiles within the compute units (4000 cells, 11200
+    // steps: 20.6 ms with 24, 21.8 with 16), 16 where none does
+    const int cus = device_cus();
     rW = 64;
     rhalo = 16;
+    for (int k = 24; k > 16; k -= 2)
+      if ((h->grid.nx + (rW - 2 * k) - 1) / (rW - 2 * k) <= cus) {
+        rhalo = k;
+        break;
+      }
     rowned = rW - 2 * rhalo;
     rtiles = (h->grid.nx + rowned - 1) / rowned;
   }

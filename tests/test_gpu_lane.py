@@ -147,3 +147,24 @@ def test_last_cell_and_small_owned_parts(orc, nx):
     ee, ep = _errs({q: v.cpu().numpy() for q, v in b.run()[0].items()}, ref)
     b.close()
     assert ee < 1e-12 and ep < 1e-12, (ee, ep)
+
+
+@pytest.mark.parametrize("n,variant,precision,tol", [(2, "quad", "fp64", 1e-10), (3, "quad", "fp64", 1e-10),
+                                                     (3, "quad_mfma", "fp32c", 1e-5), (3, "quad", "fp32cf", 1e-5),
+                                                     (2, "quad", "fp32", 1e-5), (4, "quad", "bf16x6", 1e-4)])
+def test_four_lane_boundary_cell(orc, n, variant, precision, tol):
+    """The boundary cell, which the lanes of its neighbour keep, at every kind
+    of place of a tile: probe, snapshots, and a run in uneven chunks."""
+    for nx in list(range(94, 102)) + [3, 34]:
+        p = W.random_problem(n, nx, nx=nx, nt=120)
+        s = mln.Solver(p, precision=precision, snap_every=40, variant=variant, tile=32, steps_per_launch=8)
+        a = {k: v.cpu().numpy().copy() for k, v in s.run().items()}
+        s.reset()
+        for k in (1, 38, 9):
+            s.step(k)
+        b = {k: v.cpu().numpy() for k, v in s.run().items()}
+        s.close()
+        for k in a:
+            assert np.array_equal(a[k], b[k]), (nx, k)
+        ee, ep = _errs(a, orc.run(p, snap_every=40))
+        assert ee < tol and ep < tol, (nx, ee, ep)
