@@ -466,7 +466,7 @@ def tmz_beam(reps=REPS):
                      "hbm_frac": byts / (us * 1e-6) / 8e12}
         tf = os.path.join(ROOT, "profiles", f"fwd_tmz_n3_{prec}_2d_beam_traffic.txt")
         if os.path.exists(tf):
-            out[prec]["traffic_bytes_per_step"] = measured_traffic(prec, tf, TMZ_SOURCES)
+            out[prec]["traffic_bytes_per_launch"] = measured_traffic(prec, tf, TMZ_SOURCES)
         if prec != "fp64":
             out[prec]["err_probe_vs_fp64"] = rel_err(rec[prec]["probe"], rec["fp64"]["probe"])
             out[prec]["err_pop_vs_fp64"] = float(np.max(np.abs(rec[prec]["pop"] - rec["fp64"]["pop"])))
@@ -727,7 +727,7 @@ def profile_tmz(name, nt, precision, steps, warmup):
     t = _median(ts)
     g = p.grid
     print(json.dumps({"profile_case": name, "nx": g.nx, "ny": g.ny, "nt": nt, "n_med": g.n_med,
-                      "launches_per_run": nt, "ms_per_run": t * 1e3, "us_per_step": t / nt * 1e6,
+                      "ms_per_run": t * 1e3, "us_per_step": t / nt * 1e6,
                       "cell_updates_per_s": g.n_med * nt / t, "precision": precision}))
 
 

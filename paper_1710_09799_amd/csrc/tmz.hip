@@ -223,8 +223,8 @@ int tmz_rows(const mln_tmz *t, int K, double *us) {
 }
 
 // Steps per launch: the least time per step.  Against one step per launch, us
-// per step on the beam of 2048 x 512 cells: three-level FP64 15.4 / 27.1,
-// compensated FP32 16.6 / 25.0, FP32 9.8 / 15.6.
+// per step on the beam of 2048 x 512 cells: three-level FP64 15.6 / 27.1,
+// compensated FP32 17.8 / 25.0, FP32 10.0 / 15.6.
 void tmz_shape(mln_tmz *t) {
   if (t->N > 3 || t->grid.nx > (int64_t)1 << 30) return;  // one step per launch
   double best = 0.0;
