@@ -194,10 +194,15 @@ typedef struct {
                                   wavefront as one 16 x 8 by 8 x 16 product per
                                   step, Sec. 4.1 fused half steps; tile as for
                                   3, a multiple of 16).
-                                  Automatic: quad for N <= 3 on grids below 1e5
-                                  cells (latency-bound sizes), workgroup tile on
-                                  larger ones; N = 4: wavefront tile; N = 6:
-                                  workgroup tile; split-BF16 precisions: quad    */
+                                  Automatic: quad for N <= 3 on grids that are
+                                  latency-bound (up to some 1e4 cells; 1e5 with
+                                  compensated fields or an adjoint), workgroup
+                                  tile on larger ones, where plain fields run
+                                  one wavefront per tile of 64 to 256 cells; N =
+                                  4, 6: workgroup tile (on the FP64 matrix cores
+                                  in FP64 and the compensated modes), plain FP32
+                                  of N = 4: wavefront tile; split-BF16
+                                  precisions: quad                               */
 } mln_options;
 
 /* Gradients of a scalar objective J with respect to the physical inputs (any
