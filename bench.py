@@ -462,8 +462,7 @@ def tmz_beam(reps=REPS):
         byts = (cells * 3 * 2 + g.n_med * rows * 2) * rs
         us = gt / g.nt * 1e6
         out[prec] = {"value": g.n_med * g.nt / t, "paper_P": cells * g.nt / t, "us_per_step": us,
-                     "alg_bytes_per_step": byts, "alg_GBps": byts / (us * 1e-6) / 1e9,
-                     "hbm_frac": byts / (us * 1e-6) / 8e12}
+                     "alg_bytes_per_step": byts, "alg_GBps": byts / (us * 1e-6) / 1e9}
         tf = os.path.join(ROOT, "profiles", f"fwd_tmz_n3_{prec}_2d_beam_traffic.txt")
         if os.path.exists(tf):
             out[prec]["traffic_bytes_per_launch"] = measured_traffic(prec, tf, TMZ_SOURCES)
