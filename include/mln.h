@@ -363,8 +363,8 @@ int mln_grad(mln_handle *h, const double *dJ_dprobe, mln_grads *out);
 /* Tiling of mln_grad's reverse kernel.  variant 0 (default): automatic
  * (after a four-lanes-per-cell forward kernel: 128-cell tiles and the
  * largest even step count up to 48 that keeps the tiles within the compute
- * units, 16 where none does; 64-cell tiles and 16 steps for the FP64
- * three-level reverse step; 256 cells and 16 steps after the streamed
+ * units, 16 where none does; 64-cell tiles and so up to 24 steps for
+ * the FP64 three-level reverse step; 256 cells and 16 steps after the streamed
  * forward kernel; otherwise the forward kernel's tiling); 1: one thread per cell, tile a multiple of 64 in [64,
  * 256]; 3: four lanes per cell, tile a multiple of 16 in [16, 128].  tile 0:
  * 256 (variant 1) or 128; steps_per_launch 0: tile/4; the halo is
@@ -396,8 +396,10 @@ const char *mln_last_error(void);
  *                          MLN_FP32_COMP_FIELDS or MLN_FP32_FIELDS;
  *                          route MLN_ROUTE_ROTATION; variant 0 (= 1), 1 or
  *                          3; ckpt_every 0; tile / steps_per_launch as for
- *                          mln_init (0: 256 cells for variant 1, 128 for
- *                          variant 3; 16 steps); stream shared by all problems
+ *                          mln_init (both 0: chosen from the sizes for
+ *                          variant 1 with plain fields; else 256 cells for
+ *                          variant 1, 128 for variant 3, 16 steps); stream
+ *                          shared by all problems
  * Each problem gets its own handle (device state, factors, recording), owned
  * by the batch; mln_batch_instance lends it out (do not mln_free it).
  * Errors: those of mln_init (prefixed with the problem index in
@@ -539,8 +541,10 @@ void mln_pstd_free(mln_pstd *p);
  *            d^{n+1/2} as in mln_init), nsnap = nt / snap_every (0: none)
  *   precision MLN_FP64, MLN_FP32 or MLN_FP32_COMP (MLN_ENOTSUPPORTED else)
  *   stream   hipStream_t for all device work, NULL = the default stream
- * One kernel launch per time step (64 x 4 cells per workgroup, the Bloch
- * state streamed from and to device memory each step).  Inputs are copied;
+ * N = 2, 3: several time steps per launch on register tiles (two buffers of
+ * the Bloch state; one step per launch in place where the second does not fit
+ * into device memory, and for single steps); N = 4, 6: one launch per time
+ * step.  Inputs are copied;
  * records stay owned by the caller.  Errors: MLN_EINVAL, MLN_ECOURANT,
  * MLN_ENOTSUPPORTED, the medium errors of mln_init, MLN_ENOMEM, MLN_EHIP;
  * on error *out is set to NULL. */
