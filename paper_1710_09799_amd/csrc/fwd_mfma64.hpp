@@ -33,6 +33,7 @@
 #pragma once
 
 #include "fwd_lane.hpp"
+#include "medium_cells.hpp"
 
 namespace mln {
 
@@ -101,7 +102,7 @@ __global__ void __launch_bounds__(4 * kMaxMfma64Tile / C) fwd_mfma64_kernel(FwdA
   const int64_t w0 = base + 16 * C * w;  // first cell of the wavefront
   const int64_t i0 = w0 + col;           // the lane's cell of group 0
 
-  const bool any_med = w0 < a.me && w0 + 16 * C > a.mb;
+  const bool any_med = meets_medium(w0, 16 * C, a.mb, a.me);
   const bool all_med = w0 >= a.mb && w0 + 16 * C <= a.me;
   const bool inside = w0 >= 1 && w0 + 16 * C <= a.nx - 1;  // interior cells only
   const bool has_right = base <= a.nx - 1 && base + W > a.nx - 1;
@@ -140,7 +141,7 @@ __global__ void __launch_bounds__(4 * kMaxMfma64Tile / C) fwd_mfma64_kernel(FwdA
 #pragma unroll
   for (int q = 0; q < C; ++q) {
     const int64_t i = i0 + 16 * q;
-    const int64_t im = i < a.mb ? 0 : (i < a.me ? i - a.mb : a.me - a.mb - 1);
+    const int64_t im = nearest_medium(i, a.mb, a.me);
 #pragma unroll
     for (int s = 0; s < S; ++s) {
       const int j = jr[s] >= 0 ? jr[s] : 0;
