@@ -20,6 +20,7 @@
 #pragma once
 
 #include "fwd_impl.hpp"
+#include "wide_angle.hpp"
 
 namespace mln {
 
@@ -136,58 +137,29 @@ __device__ __forceinline__ void rotate_pair(M s, M cm1, M ar, M br, M &a, M &b) 
   b += cm1 * v - s * u;
 }
 
-// sin x and cos x - 1 of any angle: x = n pi/2 + r, |r| <= pi/4, with pi/2 in
-// three parts and fused products (x - n p1 is exact: both are multiples of
-// p1's last place or of x's, and the difference is below 2), the Taylor series
-// of r to the last bit, and the quadrant.  Written out here because the device
-// library's argument reduction, inlined or called, takes registers from the
-// step loop (the three-level FP64 kernel needed 200 instead of 160, two
-// wavefronts per SIMD instead of three); its constants are read from memory in
-// the branch that takes it.
-static __device__ const double kWide64[20] = {
-    0.63661977236758134308, 0x1.921fb54442d18p+0, 0x1.1a62633145c07p-54, -0x1.f1976b7ed8fbcp-110,
-    -1.0 / 6.0, 1.0 / 120.0, -1.0 / 5040.0, 1.0 / 362880.0, -1.0 / 39916800.0, 1.0 / 6227020800.0,
-    -1.0 / 1307674368000.0, 1.0 / 355687428096000.0,
-    1.0 / 24.0, -1.0 / 720.0, 1.0 / 40320.0, -1.0 / 3628800.0, 1.0 / 479001600.0, -1.0 / 87178291200.0,
-    1.0 / 20922789888000.0, -1.0 / 6402373705728000.0};
-static __device__ const float kWide32[11] = {
-    0.636619772f, 0x1.921fb60000000p+0f, -0x1.777a5c0000000p-25f, -0x1.ee59da0000000p-50f,
-    -1.0f / 6.0f, 1.0f / 120.0f, -1.0f / 5040.0f, 1.0f / 362880.0f,
-    1.0f / 24.0f, -1.0f / 720.0f, 1.0f / 40320.0f};
-__device__ __forceinline__ void sincm1_wide(double x, double &s, double &cm1) {
-  const double *k = reread(kWide64);
-  const double n = rint(x * cld(k, 0));
-  const double r = fma(-n, cld(k, 3), fma(-n, cld(k, 2), fma(-n, cld(k, 1), x)));
-  const double r2 = r * r;
-  double ps = cld(k, 11), pc = cld(k, 19);
-#pragma unroll
-  for (int i = 10; i >= 4; --i) ps = fma(ps, r2, cld(k, i));
-#pragma unroll
-  for (int i = 18; i >= 12; --i) pc = fma(pc, r2, cld(k, i));
-  const double sr = fma(r * r2, ps, r), cr = r2 * fma(r2, pc, -0.5);  // sin r, cos r - 1
-  const double q = n - 4.0 * floor(0.25 * n);                         // n mod 4 (exact)
-  const double c1 = cr + 1.0;
-  s = q == 0.0 ? sr : (q == 1.0 ? c1 : (q == 2.0 ? -sr : -c1));
-  cm1 = q == 0.0 ? cr : (q == 1.0 ? -sr - 1.0 : (q == 2.0 ? -cr - 2.0 : sr - 1.0));
+// sin x and cos x - 1 of any angle (wide_angle.hpp), out of line; results by
+// value, in registers.
+static __device__ const double kWide[20] = MLN_WIDE_TABLE;
+static __device__ const uint32_t kTurn[40] = MLN_TURN_TABLE;
+template <typename M2, typename M>
+__device__ __forceinline__ M2 sincm1_any(M x) {
+  M2 r;
+  if (!wave_any(!(fabs(x) <= M(0.5))))
+    medium_angle(x, kWide, r.x, r.y);
+  else
+    wide_angle(x, kWide, kTurn, r.x, r.y);
+  return r;
 }
-__device__ __forceinline__ void sincm1_wide(float x, float &s, float &cm1) {
-  const float *k = reread(kWide32);
-  const float n = rintf(x * cld(k, 0));
-  const float r = fmaf(-n, cld(k, 3), fmaf(-n, cld(k, 2), fmaf(-n, cld(k, 1), x)));
-  const float r2 = r * r;
-  float ps = cld(k, 7), pc = cld(k, 10);
-#pragma unroll
-  for (int i = 6; i >= 4; --i) ps = fmaf(ps, r2, cld(k, i));
-#pragma unroll
-  for (int i = 9; i >= 8; --i) pc = fmaf(pc, r2, cld(k, i));
-  const float sr = fmaf(r * r2, ps, r), cr = r2 * fmaf(r2, pc, -0.5f);
-  const float q = n - 4.0f * floorf(0.25f * n);
-  const float c1 = cr + 1.0f;
-  s = q == 0.0f ? sr : (q == 1.0f ? c1 : (q == 2.0f ? -sr : -c1));
-  cm1 = q == 0.0f ? cr : (q == 1.0f ? -sr - 1.0f : (q == 2.0f ? -cr - 2.0f : sr - 1.0f));
+static __device__ __noinline__ double2 sincm1_wide_call(double x) { return sincm1_any<double2>(x); }
+static __device__ __noinline__ float2 sincm1_wide_call(float x) { return sincm1_any<float2>(x); }
+template <typename M>
+__device__ __forceinline__ void sincm1_wide(M x, M &s, M &cm1) {
+  const auto r = sincm1_wide_call(x);
+  s = r.x;
+  cm1 = r.y;
 }
 
-template <int N, typename M, int C, bool SERIES>
+template <int N, typename M, int C>
 __device__ __forceinline__ void rotate_cells(const CellFac<N, M> &f, const M (&E)[C], M (&z)[C][N * N - 1]) {
 #pragma unroll
   for (int p = 0; p < CellFac<N, M>::Q; ++p) {
@@ -195,19 +167,15 @@ __device__ __forceinline__ void rotate_cells(const CellFac<N, M> &f, const M (&E
 #pragma unroll
     for (int c = 0; c < C; ++c) {
       M s, cm1;
-      if constexpr (SERIES)
-        sincm1_series(th * E[c], s, cm1);
-      else
-        sincm1_wide(th * E[c], s, cm1);
+      sincm1_series(th * E[c], s, cm1);
       rotate_pair(s, cm1, ar, br, z[c][2 * p], z[c][2 * p + 1]);
     }
   }
 }
 
-// exp(U E dt) of C cells.  |E| thmax <= 1/16 in the whole wavefront (every
-// practical field): the short series without a branch per angle.
+// Whether a rotation angle of the wavefront may be beyond `limit` (or is NaN).
 template <int N, typename M, int C>
-__device__ __forceinline__ void cells_rotate(const CellFac<N, M> &f, const M (&E)[C], M (&z)[C][N * N - 1]) {
+__device__ __forceinline__ bool cells_beyond(const CellFac<N, M> &f, const M (&E)[C], M limit) {
   M em = 0;
   bool nan = false;
 #pragma unroll
@@ -216,10 +184,67 @@ __device__ __forceinline__ void cells_rotate(const CellFac<N, M> &f, const M (&E
     em = e > em ? e : em;
     nan |= e != e;
   }
-  if (__builtin_expect(!wave_any(nan || em * f.thmax > M(0.0625)), 1))
-    rotate_cells<N, M, C, true>(f, E, z);
+  return wave_any(nan || em * f.thmax > limit);
+}
+
+// How a kernel evaluates angles beyond the short series.  The branch is cold
+// in most runs, but its registers, code and calls shape the step loop around it.
+//   inlined: wide_angle at each place;  calls: a call at each place;
+//   loop: up to 1/2 rad the series at each place, beyond one call in a loop
+//   over the pairs and cells.
+// Us a run, inlined / calls / loop: beam of 2048 x 512 cells, three levels, FP64
+// 33070 / 34500 / 34300; sweep of 64 problems, FP64 13430 / 13400 / 12740;
+// spectral ring, 2048 cells 14520 / 11400 / 11890.  The loop takes 20
+// registers more than the calls, a wavefront per SIMD where the budget is
+// tight; inlined the FP64 evaluation takes FP32 kernels 45.
+enum class Wide { inlined, calls, loop };
+
+template <int N, typename M, int C, Wide HOW>
+__device__ __forceinline__ void rotate_cells_wide(const CellFac<N, M> &f, const M (&E)[C], M (&z)[C][N * N - 1]) {
+  constexpr int Q = CellFac<N, M>::Q;
+  const bool medium = HOW == Wide::loop && !cells_beyond<N, M, C>(f, E, M(0.5));
+  M s, cm1;
+  if (HOW != Wide::loop || medium) {
+#pragma unroll
+    for (int p = 0; p < Q; ++p) {
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        const M x = f.th[p] * E[c];
+        if constexpr (HOW == Wide::inlined)
+          wide_angle(x, reread(kWide), reread(kTurn), s, cm1);
+        else if constexpr (HOW == Wide::calls)
+          sincm1_wide(x, s, cm1);
+        else
+          medium_angle(x, reread(kWide), s, cm1);
+        rotate_pair(s, cm1, f.zr[2 * p], f.zr[2 * p + 1], z[c][2 * p], z[c][2 * p + 1]);
+        if constexpr (HOW == Wide::loop) __builtin_amdgcn_sched_barrier(0);  // one angle at a time: registers
+      }
+    }
+  } else {
+#pragma unroll 1
+    for (int i = 0; i < Q * C; ++i) {
+      M x = 0;
+#pragma unroll
+      for (int k = 0; k < Q * C; ++k)
+        if (k == i) x = f.th[k / C] * E[k % C];
+      sincm1_wide(x, s, cm1);
+#pragma unroll
+      for (int k = 0; k < Q * C; ++k) {
+        const int p = k / C, c = k % C;
+        if (k == i) rotate_pair(s, cm1, f.zr[2 * p], f.zr[2 * p + 1], z[c][2 * p], z[c][2 * p + 1]);
+      }
+    }
+  }
+}
+
+// exp(U E dt) of C cells.  |E| thmax <= 1/16 in the whole wavefront (every
+// practical field): the short series without a branch per angle.
+template <int N, typename M, int C, Wide HOW>
+__device__ __forceinline__ void cells_rotate(const CellFac<N, M> &f, const M (&E)[C], M (&z)[C][N * N - 1]) {
+  if (__builtin_expect(!cells_beyond<N, M, C>(f, E, M(0.0625)), 1))
+    rotate_cells<N, M, C>(f, E, z);
   else
-    rotate_cells<N, M, C, false>(f, E, z);
+    rotate_cells_wide<N, M, C, HOW>(f, E, z);
 }
 
 // Populations of one cell's rotated state, FP64.

@@ -168,7 +168,7 @@ __device__ __forceinline__ void lane_tile(const FwdArgs<Real> &a, ColdArgs<Real>
       M Em[C];
 #pragma unroll
       for (int j = 0; j < C; ++j) Em[j] = (M)E[j];
-      cells_rotate<N, M, C>(F, Em, z);
+      cells_rotate<N, M, C, C == 4 && sizeof(M) == 8 ? Wide::loop : Wide::calls>(F, Em, z);
       if (__builtin_expect(snap, 0)) {
         const ColdArgs<Real> c = cold_again<Real>(cold);
         const int64_t nmed = c->me - c->mb;

@@ -173,7 +173,8 @@ __global__ void __launch_bounds__(64 * NW) fwd_tmz_tile_kernel(TmzTileArgs<Real>
 #pragma unroll
           for (int k = 0; k < D; ++k) y[c][k] = z[q + c][k];
         }
-        cells_rotate<N, M, G>(F, e, y);
+        // (six rows per lane fill the registers and spill around calls)
+        cells_rotate<N, M, G, C == 6 ? Wide::inlined : Wide::calls>(F, e, y);
         if (__builtin_expect(snap, 0)) {
           const TmzCold<Real> cq = tmz_again<Real>(cold);
           double *pop = cq->a.pop_out;
@@ -321,7 +322,7 @@ __global__ void __launch_bounds__(kTmzTX * kTmzTY) fwd_tmz_one_kernel(TmzArgs<Re
       z[0][k] = (M)zh[k];
       if constexpr (COMP) z[0][k] += (M)zl[k];
     }
-    cells_rotate<N, M, 1>(F, e, z);
+    cells_rotate<N, M, 1, sizeof(M) == 8 ? Wide::inlined : Wide::calls>(F, e, z);
     if (a.snap && a.pop_out && med) cells_record<N, M>(a.fac.pop, a.fac.popc, z[0], a.pop_out + a.snap_i * N * nmed + m, nmed);
     cells_shared<N, M, COMP, 1>(F, K, z, P);
     P[0] = med ? P[0] : M(0);

@@ -4,12 +4,7 @@
 
 #include <cstdint>
 
-#if defined(__HIPCC__)
-#include <hip/hip_runtime.h>
-#define MLN_HD __host__ __device__ __forceinline__
-#else
-#define MLN_HD inline
-#endif
+#include "host_device.hpp"
 
 namespace mln {
 
