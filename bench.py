@@ -76,7 +76,7 @@ def source_hash(files):
     return h.hexdigest()
 
 
-TMZ_SOURCES = ["fwd_tmz_tile.hpp", "fwd_tmz.hpp", "cells.hpp", "wide_angle.hpp", "fwd_impl.hpp", "fwd_kernels.hpp", "tmz.hip"]
+TMZ_SOURCES = ["fwd_tmz_tile.hpp", "fwd_tmz.hpp", "cells.hpp", "wide_angle.hpp", "float_pair.hpp", "fwd_impl.hpp", "fwd_kernels.hpp", "tmz.hip"]
 STREAM_SOURCES = ["fwd_stream.hpp", "fwd_impl.hpp", "fwd_kernels.hpp", "stream.hip"]
 
 

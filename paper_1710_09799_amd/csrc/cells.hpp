@@ -19,6 +19,7 @@
 // is rounded to what a pair holds after every step (pair_exact).
 #pragma once
 
+#include "float_pair.hpp"
 #include "fwd_impl.hpp"
 #include "wide_angle.hpp"
 
@@ -43,15 +44,6 @@ struct CellType<float, true> {
   typedef double type;
 };
 
-// A value that a pair of floats holds exactly: multiples of the smallest
-// float (the added constant's last place is 2^-149; it changes nothing above
-// 2^-44), then 48 bits.  The compensated state is rounded so after every step,
-// so that a launch boundary, where it is stored, does not change the result.
-__device__ __forceinline__ double pair_exact(double x) {
-  const double m = 0x1.8p-97;
-  const double r = (x + m) - m;
-  return __hiloint2double(__double2hiint(r), __double2loint(r) & ~31);
-}
 __device__ __forceinline__ float pair_exact(float x) { return x; }
 
 // The factors of the step in the arithmetic type M.  Those of N = 2 are held
