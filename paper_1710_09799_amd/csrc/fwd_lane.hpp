@@ -6,12 +6,13 @@
 // LDS exchanges per step and reads the shared factor from LDS for every cell.
 // Here a lane's neighbours are its own registers except at its two ends,
 // which a wavefront shift (DPP) passes on; the H face left of the lane's first
-// cell is a private copy, updated with the operands its owner uses, so there
-// is no barrier and no LDS; and the medium step takes the C cells together
-// (cells.hpp).  Tiles inside the grid whose cells are all medium (or all
-// vacuum) take no per-cell test.  Temporal blocking as in the other tile
-// kernels: nsteps <= halo steps per launch, the owned central cells written
-// back.
+// cell is a private copy, updated with the operands its owner uses, so a step
+// has no barrier and no exchange through LDS (which holds the launch's source
+// samples in the tiles at the grid's ends); and the medium step takes the C
+// cells together (cells.hpp).  Tiles inside the grid whose cells are all medium
+// (or all vacuum) take no per-cell test.  Temporal blocking as in the other
+// tile kernels: nsteps <= halo steps per launch, the owned central cells
+// written back.
 //
 // The scalar registers bound the step loop (they hold the factors, the series'
 // constants and the update coefficients), so what only a recording step, the
@@ -125,6 +126,7 @@ __device__ __forceinline__ void lane_tile(const FwdArgs<Real> &a, ColdArgs<Real>
       }
     }
     for (int i = lane; i < nsteps; i += 64) sSrc[i] = a.src[step0 + 1 + i];
+    lds_barrier();  // one wavefront: orders the writes before the other lanes' reads
   }
   // per-lane roles of the C cells, one bit each: medium, interior (Yee
   // update), cell 0, cell nx-1
