@@ -126,7 +126,9 @@ __device__ __forceinline__ void lane_tile(const FwdArgs<Real> &a, ColdArgs<Real>
       }
     }
     for (int i = lane; i < nsteps; i += 64) sSrc[i] = a.src[step0 + 1 + i];
-    lds_barrier();  // one wavefront: orders the writes before the other lanes' reads
+    // (one wavefront: orders the writes before the other lanes' reads)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   }
   // per-lane roles of the C cells, one bit each: medium, interior (Yee
   // update), cell 0, cell nx-1
