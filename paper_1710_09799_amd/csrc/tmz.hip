@@ -164,6 +164,7 @@ TmzArgs<Real> tmz_args(mln_tmz *t, const FacDev<Real> &fd, const Real (&c)[7]) {
   a.mx1 = t->grid.mx1;
   a.my0 = t->grid.my0;
   a.my1 = t->grid.my1;
+  if (t->nmed == 0) a.mx0 = a.mx1 = 0x7fffff00;  // no tile crosses a medium of no cells
   a.ld = t->ld;
   a.chx = c[0];
   a.chy = c[1];
