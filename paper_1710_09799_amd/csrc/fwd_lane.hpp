@@ -97,19 +97,35 @@ __device__ __forceinline__ void lane_tile(const FwdArgs<Real> &a, ColdArgs<Real>
   Real E[C], H[C];
   M z[C][D];
   Real Hl = 0;
+  // the compensated state's floats, all under way before the first is summed
+  Real zh[COMP ? D : 1][C], zl[COMP ? D : 1][C];
   if (inside && (all_med || !any_med)) {  // whole runs of C cells
     load_run<C>(a.Ein + g0, E);
     load_run<C>(a.Hin + g0, H);
     Hl = a.Hin[g0 - 1];
+    if constexpr (COMP) {
+      if (all_med) {
 #pragma unroll
-    for (int i = 0; i < D; ++i) {
-      Real t[C], tl[C];
+        for (int i = 0; i < D; ++i) {
+          load_run<C>(a.zin + i * a.ld + (g0 - a.mb), zh[i]);
+          load_run<C>(a.zin + (D + i) * a.ld + (g0 - a.mb), zl[i]);
+        }
+      } else {
 #pragma unroll
-      for (int j = 0; j < C; ++j) t[j] = tl[j] = 0;
-      if (all_med) load_run<C>(a.zin + i * a.ld + (g0 - a.mb), t);
-      if (COMP && all_med) load_run<C>(a.zin + (D + i) * a.ld + (g0 - a.mb), tl);
+        for (int i = 0; i < D; ++i)
 #pragma unroll
-      for (int j = 0; j < C; ++j) z[j][i] = COMP ? (M)t[j] + (M)tl[j] : (M)t[j];
+          for (int j = 0; j < C; ++j) zh[i][j] = zl[i][j] = 0;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < D; ++i) {
+        Real t[C];
+#pragma unroll
+        for (int j = 0; j < C; ++j) t[j] = 0;
+        if (all_med) load_run<C>(a.zin + i * a.ld + (g0 - a.mb), t);
+#pragma unroll
+        for (int j = 0; j < C; ++j) z[j][i] = t[j];
+      }
     }
   } else {
     if (g0 - 1 >= 0 && g0 - 1 <= a.nx - 2) Hl = a.Hin[g0 - 1];
@@ -121,14 +137,24 @@ __device__ __forceinline__ void lane_tile(const FwdArgs<Real> &a, ColdArgs<Real>
       H[j] = (g >= 0 && g <= a.nx - 2) ? a.Hin[g] : Real(0);
 #pragma unroll
       for (int i = 0; i < D; ++i) {
-        z[j][i] = med ? (M)a.zin[i * a.ld + (g - a.mb)] : M(0);
-        if (COMP && med) z[j][i] += (M)a.zin[(D + i) * a.ld + (g - a.mb)];
+        if constexpr (COMP) {
+          zh[i][j] = med ? a.zin[i * a.ld + (g - a.mb)] : Real(0);
+          zl[i][j] = med ? a.zin[(D + i) * a.ld + (g - a.mb)] : Real(0);
+        } else {
+          z[j][i] = med ? a.zin[i * a.ld + (g - a.mb)] : Real(0);
+        }
       }
     }
     for (int i = lane; i < nsteps; i += 64) sSrc[i] = a.src[step0 + 1 + i];
     // (one wavefront: orders the writes before the other lanes' reads)
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
+  }
+  if constexpr (COMP) {
+#pragma unroll
+    for (int j = 0; j < C; ++j)
+#pragma unroll
+      for (int i = 0; i < D; ++i) z[j][i] = (M)zh[i][j] + (M)zl[i][j];
   }
   // per-lane roles of the C cells, one bit each: medium, interior (Yee
   // update), cell 0, cell nx-1
