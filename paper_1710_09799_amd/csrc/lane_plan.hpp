@@ -18,17 +18,16 @@ namespace mln {
 inline bool lane_better(int W, int64_t ntiles, int cus) { return W <= 128 || ntiles >= 3 * (int64_t)cus; }
 
 // Smallest grid that the automatic choice gives to the one-wavefront kernel
-// (four lanes per cell below): where the measured rates cross,
-// cell-updates/s lane / quad.  Two-level: FP64 and the compensated state 4000
-// cells 4.7e9 / 4.1e9, 20000 cells 2.2e10 / 1.7e10; FP32 12000 cells 1.46e10 /
-// 1.44e10.  Three-level: FP64 24000 cells 2.7e10 / 2.5e10 (at 20000 cells the
-// four-lane kernel's 228 tiles just fit the compute units: 2.3e10 / 2.7e10);
-// FP32 30000 cells 3.9e10 / 4.6e10, 36000 cells 4.1e10 / 3.8e10; compensated
-// (its product on the matrix cores) 36000 cells 3.2e10 / 3.2e10, 50000 cells
-// 3.9e10 / 3.7e10.
+// (four lanes per cell below): where the measured times cross, us per step
+// one wavefront / four lanes.  Two-level: FP64 22000 cells 0.65 / 0.64, 24000
+// 0.66 / 0.74; compensated 20000 cells 0.70 / 0.62, 25000 0.72 / 0.85; FP32 23000
+// cells 0.60 / 0.56, 25000 0.56 / 0.69 (and 32000 0.56 / 0.54).  Three-level:
+// FP64 22500 cells 0.92 / 0.81, 24000 0.90 / 0.93; FP32 36000 cells 0.88 / 0.79,
+// 40000 0.90 / 0.94; compensated (its product on the matrix cores) 40000 cells
+// 1.19 / 1.12, 45000 1.33 / 1.16, 60000 1.46 / 1.38, 75000 1.49 / 1.72.
 inline int64_t lane_min_cells(int N, bool fp32_plain, bool comp) {
-  if (N == 2) return fp32_plain ? 12000 : 3000;
-  return fp32_plain ? 33000 : (comp ? 40000 : 23000);
+  if (N == 2) return fp32_plain ? 24000 : 23000;
+  return fp32_plain ? 38000 : (comp ? 45000 : 23000);
 }
 
 struct LanePlan {
