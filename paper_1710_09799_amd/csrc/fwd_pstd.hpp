@@ -325,8 +325,20 @@ __device__ __forceinline__ void pstd_pack(double2 Gk, double2 Gm, double2 w, dou
 // N levels, C cells per thread (blockDim.x = nx / C <= TMAX threads).  With
 // TMAX = 256 a workgroup is one wavefront per SIMD, which may hold up to 512
 // registers per lane (VGPRs and AGPRs); with 512, two per SIMD share them.
+// Wavefronts per SIMD that an instance is compiled for at least: those that
+// batches of problems fill and that the unrolled transforms would cost.  Us per
+// step of 300 problems without / with it: N = 4, 1024 cells, 256 threads 15.3 /
+// 11.5; N = 2, 2048 cells, 256 threads 10.4 / 6.6; N = 2, 1024 cells, 512
+// threads 6.4 / 4.0.
 template <int N, int C, int TMAX>
-__global__ void __launch_bounds__(TMAX) fwd_pstd_kernel(PstdArgs a) {
+constexpr int pstd_waves() {
+  if (N == 2) return C == 8 && TMAX == 256 ? 2 : (C == 2 && TMAX == 512 ? 4 : 1);
+  return N == 4 && C == 4 && TMAX == 256 ? 2 : 1;
+}
+
+template <int N, int C, int TMAX>
+__global__ void __launch_bounds__(TMAX) __attribute__((amdgpu_waves_per_eu(pstd_waves<N, C, TMAX>())))
+fwd_pstd_kernel(PstdArgs a) {
   constexpr int D = N * N - 1;
   constexpr int R = (C + 3) / 4;  // mode pairs per thread: (M / 2) / T rounded up
   // the medium step of N = 2, 3: cells.hpp, the factor in registers
