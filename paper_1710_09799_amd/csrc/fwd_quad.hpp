@@ -130,8 +130,8 @@ struct MfAcc<double> {
 };
 
 // One tile (index `tile` of the problem described by `a`) on one workgroup of
-// 4 W lanes.
-template <int N, typename Real, bool COMP, bool CF, bool MF = false>
+// 4 W lanes.  TAPE: the launch writes the tape.
+template <int N, typename Real, bool COMP, bool CF, bool MF = false, bool TAPE = false>
 __device__ __forceinline__ void quad_tile(const FwdArgs<Real> &a, int64_t tile) {
   constexpr int D = N * N - 1, Q = N * (N - 1) / 2;
   static_assert(D <= 8, "four lanes of two components each");
@@ -311,7 +311,7 @@ __device__ __forceinline__ void quad_tile(const FwdArgs<Real> &a, int64_t tile) 
       // cell's own role (is_med, owned) only selects what is kept
       if (tile_med) {
         mf_apply();
-        if (__builtin_expect(a.tape != nullptr, 0)) {
+        if constexpr (TAPE) {
           const int64_t n = a.step0 + s;
           if (owned && is_med && n >= a.tape_step0) {
             Real *tp = a.tape + (n - a.tape_step0) * (D + 1) * a.ld + c;
@@ -359,7 +359,7 @@ __device__ __forceinline__ void quad_tile(const FwdArgs<Real> &a, int64_t tile) 
     } else if (tile_med && is_med) {
       // (the DPP kernel keeps the per-cell branch: measured faster here
       // than the branch-free form the matrix-core kernel uses)
-      if (__builtin_expect(a.tape != nullptr, 0)) {
+      if constexpr (TAPE) {
         const int64_t n = a.step0 + s;
         if (owned && n >= a.tape_step0) {
           Real *tp = a.tape + (n - a.tape_step0) * (D + 1) * a.ld + c;
@@ -507,9 +507,14 @@ __device__ __forceinline__ void quad_tile(const FwdArgs<Real> &a, int64_t tile) 
 // FP64 and two-float-field step loops free of spills but leaves room for
 // one such workgroup per compute unit; LB = 1024 (at most 128 VGPRs) lets
 // two 512-lane workgroups share a compute unit.
-template <int N, typename Real, bool COMP, bool CF = false, int LB = 1024, bool MF = false>
-__global__ void __launch_bounds__(LB) fwd_quad_kernel(FwdArgs<Real> a) {
-  quad_tile<N, Real, COMP, CF, MF>(a, blockIdx.x);
+// TAPE: launches that write the tape run beside the reverse kernel; with at most
+// 96 registers the plain FP32 one shares its compute units (three levels, 20000
+// cells, run and gradient: 2.61 us per step with 115, 2.40 with 96).
+template <int N, typename Real, bool COMP, bool CF = false, int LB = 1024, bool MF = false, bool TAPE = false>
+__global__ void __launch_bounds__(LB)
+    __attribute__((amdgpu_waves_per_eu(TAPE && sizeof(Real) == 4 && !COMP && !CF ? 5 : LB / 256)))
+    fwd_quad_kernel(FwdArgs<Real> a) {
+  quad_tile<N, Real, COMP, CF, MF, TAPE>(a, blockIdx.x);
 }
 
 // The LB = 512 instance for tiles of at most 128 cells when every tile has a
@@ -518,16 +523,23 @@ __global__ void __launch_bounds__(LB) fwd_quad_kernel(FwdArgs<Real> a) {
 // compensated-FP32 state fits 128 VGPRs and runs faster there); else LB = 1024.
 // MF (the matrix-core product): one build, LB = 1024 (the factor rows are
 // two registers instead of 32).
+template <int N, typename Real, bool COMP, bool CF, bool TAPE>
+hipError_t launch_quad_of(int W, const FwdArgs<Real> &a, int64_t nblocks, hipStream_t st, bool mf) {
+  constexpr bool wide = std::is_same<Real, double>::value || CF;
+  const dim3 grid((unsigned)nblocks), block(4 * W);
+  if (mf)
+    hipLaunchKernelGGL((fwd_quad_kernel<N, Real, COMP, CF, 1024, true, TAPE>), grid, block, 0, st, a);
+  else if (wide && 4 * W <= 512 && nblocks <= device_cus())
+    hipLaunchKernelGGL((fwd_quad_kernel<N, Real, COMP, CF, 512, false, TAPE>), grid, block, 0, st, a);
+  else
+    hipLaunchKernelGGL((fwd_quad_kernel<N, Real, COMP, CF, 1024, false, TAPE>), grid, block, 0, st, a);
+  return hipGetLastError();
+}
+
 template <int N, typename Real, bool COMP, bool CF>
 hipError_t launch_quad(int W, const FwdArgs<Real> &a, int64_t nblocks, hipStream_t st, bool mf = false) {
-  constexpr bool wide = std::is_same<Real, double>::value || CF;
-  if (mf)
-    hipLaunchKernelGGL((fwd_quad_kernel<N, Real, COMP, CF, 1024, true>), dim3((unsigned)nblocks), dim3(4 * W), 0, st, a);
-  else if (wide && 4 * W <= 512 && nblocks <= device_cus())
-    hipLaunchKernelGGL((fwd_quad_kernel<N, Real, COMP, CF, 512>), dim3((unsigned)nblocks), dim3(4 * W), 0, st, a);
-  else
-    hipLaunchKernelGGL((fwd_quad_kernel<N, Real, COMP, CF, 1024>), dim3((unsigned)nblocks), dim3(4 * W), 0, st, a);
-  return hipGetLastError();
+  return a.tape ? launch_quad_of<N, Real, COMP, CF, true>(W, a, nblocks, st, mf)
+                : launch_quad_of<N, Real, COMP, CF, false>(W, a, nblocks, st, mf);
 }
 
 }  // namespace mln
