@@ -110,7 +110,7 @@ __global__ void __launch_bounds__(4 * kMaxMfmaqTile) fwd_mfmaq_kernel(FwdArgs<fl
   // (E, low part of E) of cell c at index c + 1; indices 0 and W + 1 stay zero
   __shared__ float2 sE[2][kMaxMfmaqTile + 2];
   __shared__ float sSrc[kMaxStepsPerLaunch], sSrcl[kMaxStepsPerLaunch];
-  __shared__ double sPr[kMaxStepsPerLaunch];  // the launch's probe values, stored after the step loop
+  __shared__ float sMur, sMurl;
   // per-slot constants (slot order): (reference state, polarisation weight,
   // constant term, its low part); per lane and pair: (theta dt, low part)
   __shared__ float4 sCst[K];
@@ -153,10 +153,6 @@ __global__ void __launch_bounds__(4 * kMaxMfmaqTile) fwd_mfmaq_kernel(FwdArgs<fl
   const bool tile_med = (base < a.me) && (base + W > a.mb);
   const bool has_right = (base <= a.nx - 1) && (base + W > a.nx - 1);
   const bool owned = in_dom && cl >= a.halo && cl < a.halo + a.owned;
-  // the boundary cell nx-1 belongs to the lanes of cell nx-2 (as in
-  // fwd_quad.hpp): no second barrier in the tile that every launch waits for
-  const bool mur = g == a.nx - 2;
-  const bool mur_owned = mur && cl + 1 >= a.halo && cl + 1 < a.halo + a.owned;
   const int64_t c = g - a.mb;
   const int64_t nmed = a.me - a.mb;
 
@@ -216,13 +212,8 @@ __global__ void __launch_bounds__(4 * kMaxMfmaqTile) fwd_mfmaq_kernel(FwdArgs<fl
 
   // fields (float-float), private copy of the left H face, state slots
   float E = 0, H = 0, Hl = 0, Elo = 0, Hlo = 0, Hll = 0;
-  float Eb = 0, Ebl = 0;  // mur: E of the boundary cell
   if (in_dom) {
     E = a.Ein[g];
-    if (mur) {
-      Eb = a.Ein[g + 1];
-      Ebl = a.Ein[a.nx + g + 1];
-    }
     Elo = a.Ein[a.nx + g];
     if (g <= a.nx - 2) {
       H = a.Hin[g];
@@ -250,7 +241,7 @@ __global__ void __launch_bounds__(4 * kMaxMfmaqTile) fwd_mfmaq_kernel(FwdArgs<fl
     if (r == 0) sE[b][cl + 1] = make_float2(E, Elo);
     lds_barrier();
     const float2 eL = sE[b][cl], eR = sE[b][cl + 2];
-    const float El = eL.x, Ell = eL.y, Er = mur ? Eb : eR.x, Erl = mur ? Ebl : eR.y;
+    const float El = eL.x, Ell = eL.y, Er = eR.x, Erl = eR.y;
     if (in_dom) {
       if (g >= 1) add_comp(Hl, Hll, a.ch * ((E - El) + (Elo - Ell)));
       if (g <= a.nx - 2) add_comp(H, Hlo, a.ch * ((Er - E) + (Erl - Elo)));
@@ -286,7 +277,7 @@ __global__ void __launch_bounds__(4 * kMaxMfmaqTile) fwd_mfmaq_kernel(FwdArgs<fl
       for (int i = 0; i < USED; ++i) pw += cst[i].y * (y[i] + d[i]);
       const float qs = quad_sum(pw);  // every lane of the tile takes part
       if (is_med) P = a.fac.p0 + qs;
-      if (__builtin_expect(snap, 0)) if (owned && is_med && a.pop_out) {
+      if (snap && owned && is_med && a.pop_out) {
         // populations of d^{n+1/2} in FP64: low parts of y'' are l + the
         // rounding error of y + d (two-sum); partial sums over this lane's
         // slots, completed over the quad
@@ -422,32 +413,26 @@ __global__ void __launch_bounds__(4 * kMaxMfmaqTile) fwd_mfmaq_kernel(FwdArgs<fl
         }
       }
     }
-    if (has_right) {  // first-order Mur boundary at cell nx-1 (kept by the lanes of cell nx-2 only)
-      float eb = Eold, ebl = Eoldl;
-      add_comp(eb, ebl, a.kmur * ((E - Eb) + (Elo - Ebl)));
-      Eb = eb;
-      Ebl = ebl;
-      if (mur && r == 0) sPr[s] = (double)Eb + (double)Ebl;
-    }
-    if (__builtin_expect(snap, 0)) {
-      if (r == 0 && a.e_out) {
-        if (owned && g != a.nx - 1) a.e_out[si * a.nx + g] = (double)E + (double)Elo;
-        if (mur_owned) a.e_out[si * a.nx + g + 1] = (double)Eb + (double)Ebl;
+    if (has_right) {  // first-order Mur boundary at cell nx-1
+      if (g == a.nx - 2 && r == 0) {
+        sMur = E;
+        sMurl = Elo;
       }
+      lds_barrier();
+      if (g == a.nx - 1) {
+        E = El;
+        Elo = Ell;
+        add_comp(E, Elo, a.kmur * ((sMur - Eold) + (sMurl - Eoldl)));
+        if (a.probe_out && owned && r == 0) a.probe_out[n + 1] = (double)E + (double)Elo;
+      }
+    }
+    if (snap) {
+      if (owned && r == 0 && a.e_out) a.e_out[si * a.nx + g] = (double)E + (double)Elo;
       snap_next += a.snap_every;
       ++si;
     }
   }
-  if (mur_owned && r == 0) {
-    a.Eout[g + 1] = Eb;
-    a.Eout[a.nx + g + 1] = Ebl;
-  }
-  // (the tile that owns the boundary cell: uniform)
-  if (a.probe_out && a.nx - 1 - base >= a.halo && a.nx - 1 - base < a.halo + a.owned) {
-    lds_barrier();
-    for (int s = threadIdx.x; s < a.nsteps; s += blockDim.x) a.probe_out[a.step0 + 1 + s] = sPr[s];
-  }
-  if (owned && g != a.nx - 1) {
+  if (owned) {
     if (r == 0) {
       a.Eout[g] = E;
       a.Eout[a.nx + g] = Elo;
