@@ -542,10 +542,10 @@ void mln_pstd_free(mln_pstd *p);
  *   precision MLN_FP64, MLN_FP32 or MLN_FP32_COMP (MLN_ENOTSUPPORTED else)
  *   stream   hipStream_t for all device work, NULL = the default stream
  * N = 2, 3: several time steps per launch on register tiles (two buffers of
- * the Bloch state; one step per launch in place where the second does not fit
- * into device memory, and for single steps); N = 4, 6: one launch per time
- * step.  Inputs are copied;
- * records stay owned by the caller.  Errors: MLN_EINVAL, MLN_ECOURANT,
+ * the Bloch state; one step per launch in place where the second would take
+ * more than an eighth of the free device memory, and for single steps); N = 4,
+ * 6: one launch per time step.  Inputs are copied; records stay owned by the
+ * caller.  Errors: MLN_EINVAL, MLN_ECOURANT,
  * MLN_ENOTSUPPORTED, the medium errors of mln_init, MLN_ENOMEM, MLN_EHIP;
  * on error *out is set to NULL. */
 typedef struct {

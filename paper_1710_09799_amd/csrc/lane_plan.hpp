@@ -30,6 +30,12 @@ inline int64_t lane_min_cells(int N, bool fp32_plain, bool comp) {
   return fp32_plain ? 38000 : (comp ? 45000 : 23000);
 }
 
+// Whether a solver may take `bytes` more for a second state buffer that it can
+// do without: at most an eighth of the device memory that is free, so that
+// what the caller allocates next still fits (several steps per launch are worth
+// 1.7x on the 2-D grid; a state of that size fills 36 GB).
+inline bool second_buffer_fits(uint64_t bytes, uint64_t free_bytes) { return bytes <= free_bytes / 8; }
+
 struct LanePlan {
   int W, K;  // cells per tile, steps per launch
 };

@@ -401,7 +401,10 @@ int mln_tmz_init(const mln_medium *medium, const mln_tmz_grid *grid, const mln_t
   const size_t zb = (size_t)(t->comp ? 2 * D : D) * t->ld * t->rs;
   HIP_TRY(t->z[0].alloc(zb));
   if (t->rows) {
-    const hipError_t e = t->z[1].alloc(zb);
+    size_t free_bytes = 0, total = 0;
+    HIP_TRY(hipMemGetInfo(&free_bytes, &total));
+    hipError_t e = hipErrorOutOfMemory;
+    if (second_buffer_fits(zb, free_bytes)) e = t->z[1].alloc(zb);
     if (e == hipErrorOutOfMemory) {  // no room for a second state: one step per launch, in place
       (void)hipGetLastError();
       t->z[1].p = nullptr;

@@ -11,6 +11,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 SHIM = """
 #include "lane_plan.hpp"
 extern "C" long min_cells(int n, int fp32, int comp) { return mln::lane_min_cells(n, fp32, comp); }
+extern "C" int fits(unsigned long bytes, unsigned long free_bytes) { return mln::second_buffer_fits(bytes, free_bytes); }
 extern "C" void plan(int n, int fp32, int bytes, long nx, int cus, int *w, int *k) {
   const mln::LanePlan p = mln::lane_plan(n, fp32, bytes, nx, cus);
   *w = p.W; *k = p.K;
@@ -46,3 +47,22 @@ def test_faster_kernel_is_chosen(lib, n, precision):
     least = lib.min_cells(n, precision == "fp32", precision == "fp32c")
     for nx, (wave, quad) in MEASURED[(n, precision)].items():
         assert (nx >= least) == (wave < quad), (nx, least)
+
+
+@pytest.mark.parametrize("state", [10**6, 5 * 10**7, 10**9, 3 * 10**10, 10**11, 2 * 10**11])
+def test_second_buffer_leaves_room(lib, state):
+    """Handles of one state each on a card of 288 GB: the second buffers never
+    take more than an eighth of what is free, and handles whose states would
+    have filled the card still find seven eighths of it."""
+    lib.fits.argtypes = [ctypes.c_ulong] * 2
+    free, handles = 288 * 10**9, 0
+    while free >= state and handles < 10000:
+        free -= state
+        handles += 1
+        if lib.fits(state, free):
+            assert 8 * state <= free
+            free -= state
+    assert free < state or handles == 10000
+    alone = min(10000, 288 * 10**9 // state)
+    if 9 * state > 288 * 10**9:  # a state beyond an eighth of the rest: as many as without the rule
+        assert handles == alone
