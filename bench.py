@@ -626,7 +626,7 @@ PROFILE_CASES = {
                                                    steps_per_launch=24)),
     "n3_fp32c_dpp": ("three_level", dict(nt=20000), dict(precision="fp32c", variant="quad", tile=128,
                                                        steps_per_launch=20)),
-    "n6_fp64": ("six_level", dict(nt=1600), dict(precision="fp64", variant="block", tile=256, steps_per_launch=16)),
+    "n6_fp64": ("six_level", dict(nt=1600), dict(precision="fp64")),
     "n6_bf16x6": ("six_level", dict(nt=1800), dict(precision="bf16x6", tile=256, steps_per_launch=30)),
     "n6_bf16x3": ("six_level", dict(nt=1800), dict(precision="bf16x3", tile=256, steps_per_launch=30)),
     "n2_large_fp64_stream": ("n2_large", {}, dict(precision="fp64", variant="stream")),
@@ -635,12 +635,9 @@ PROFILE_CASES = {
     "n2_large_fp64_k16": ("n2_large", {}, dict(precision="fp64", variant="block", tile=256, steps_per_launch=16)),
     "n2_large_fp32_k1": ("n2_large", {}, dict(precision="fp32", variant="block", tile=256, steps_per_launch=1)),
     "n2_large_fp32_k16": ("n2_large", {}, dict(precision="fp32", variant="block", tile=256, steps_per_launch=16)),
-    # pseudo-spectral ring (2048 cells, 2048 of its 8192 steps): the problem
-    # alone, its field part alone (one medium cell), and 256 problems at once
-    # the 64-problem sweep at the shape the autotuner picks (one cell per
-    # thread, tile 256, 16 steps per launch), 2048 of its 20000 steps
-    "batch64_fp64": ("batch", dict(nt=2048), dict(precision="fp64", variant="block", tile=256, steps_per_launch=16)),
-    "batch64_fp32c": ("batch", dict(nt=2048), dict(precision="fp32c", variant="block", tile=256, steps_per_launch=16)),
+    # the 64-problem sweep in the automatic shape, 2048 of its 20000 steps
+    "batch64_fp64": ("batch", dict(nt=2048), dict(precision="fp64")),
+    "batch64_fp32c": ("batch", dict(nt=2048), dict(precision="fp32c")),
     # the 2-D TMz beam workload (2048 x 512 cells), 512 of its 4096 steps
     "tmz_fp64": ("tmz", dict(nt=512), dict(precision="fp64")),
     "tmz_fp32": ("tmz", dict(nt=512), dict(precision="fp32")),
@@ -649,6 +646,8 @@ PROFILE_CASES = {
     "pol2_fp64": ("pol2", dict(nt=4000, k=24, lanes=4), {}),
     "pol2_fp64_one_lane": ("pol2", dict(nt=4000, k=64, lanes=1), {}),
     "pol2_fp64_one_step": ("pol2", dict(nt=4000, k=1, lanes=1), {}),
+    # pseudo-spectral ring (2048 cells, 2048 of its 8192 steps): the problem
+    # alone, its field part alone (one medium cell), and 256 problems at once
     "pstd_n3_ring": ("pstd", dict(batch=1, med=True), dict(steps_per_launch=256)),
     "pstd_n3_ring_fields": ("pstd", dict(batch=1, med=False), dict(steps_per_launch=256)),
     "pstd_n3_ring_batch256": ("pstd", dict(batch=256, med=True), dict(steps_per_launch=256)),

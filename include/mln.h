@@ -167,7 +167,11 @@ typedef struct {
 typedef struct {
   int32_t precision;           /* mln_precision                                    */
   int32_t route;               /* mln_route                                        */
-  int32_t steps_per_launch;    /* time steps fused into one launch (0 = automatic) */
+  int32_t steps_per_launch;    /* time steps fused into one launch (0 = automatic);
+                                  an upper bound: the tiled kernels lower it where
+                                  the boundary cell nx-1 would be a tile's first
+                                  owned cell with any division of the grid
+                                  (mln_get_config tells the count in force)      */
   int32_t tile;                /* cells per workgroup tile (0 = automatic)         */
   void *stream;                /* hipStream_t, NULL = default stream               */
   int32_t ckpt_every;          /* > 0: mln_run keeps a full-state checkpoint every
@@ -195,8 +199,8 @@ typedef struct {
                                   step, Sec. 4.1 fused half steps; tile as for
                                   3, a multiple of 16).
                                   Automatic: quad for N <= 3 on grids that are
-                                  latency-bound (up to some 1e4 cells; 1e5 with
-                                  compensated fields or an adjoint), workgroup
+                                  latency-bound (up to some 23000 to 45000 cells;
+                                  1e5 with compensated fields or an adjoint), workgroup
                                   tile on larger ones, where plain fields run
                                   one wavefront per tile of 64 to 256 cells; N =
                                   4, 6: workgroup tile (on the FP64 matrix cores
@@ -365,10 +369,12 @@ int mln_grad(mln_handle *h, const double *dJ_dprobe, mln_grads *out);
  * largest even step count up to 48 that keeps the tiles within the compute
  * units, 16 where none does; 64-cell tiles and so up to 24 steps for
  * the FP64 three-level reverse step; 256 cells and 16 steps after the streamed
- * forward kernel; otherwise the forward kernel's tiling); 1: one thread per cell, tile a multiple of 64 in [64,
- * 256]; 3: four lanes per cell, tile a multiple of 16 in [16, 128].  tile 0:
- * 256 (variant 1) or 128; steps_per_launch 0: tile/4; the halo is
- * steps_per_launch cells on each side, so 2 steps_per_launch < tile.  The
+ * forward kernel; otherwise the forward kernel's tiling); 1: one thread per
+ * cell, tile a multiple of 64 in [64, 256]; 3: four lanes per cell, tile a
+ * multiple of 16 in [16, 128].  tile 0: 256 (variant 1) or 128;
+ * steps_per_launch 0: tile/4; the halo is steps_per_launch cells on each side,
+ * so 2 steps_per_launch < tile.  steps_per_launch is an upper bound, as in
+ * mln_options (here the boundary cell must not be the first beyond a tile).  The
  * tape is read by cell, so the reverse tiling is independent of the forward
  * one; every tiling gives the same gradient to rounding.  Errors:
  * MLN_EINVAL, MLN_ENOTSUPPORTED (route or N the adjoint does not cover). */
@@ -419,8 +425,9 @@ int mln_batch_tune(mln_batch *b, int32_t trial_steps, int32_t *variant, int32_t 
 
 /* Set the kernel variant (1: one cell per thread, tile a multiple of 64 in
  * [64, 256]; 3: four lanes per cell, tile a multiple of 16 in [32, 256]) and
- * tile shape explicitly (batch at step 0) / read them back together with the
- * number of workgroups of one launch. */
+ * tile shape explicitly (batch at step 0; steps_per_launch is an upper bound,
+ * as in mln_options, and the problems take the least of theirs) / read those in
+ * force back together with the number of workgroups of one launch. */
 int mln_batch_configure(mln_batch *b, int32_t variant, int32_t tile, int32_t steps_per_launch);
 int mln_batch_get_config(const mln_batch *b, int32_t *variant, int32_t *tile,
                          int32_t *steps_per_launch, int64_t *workgroups);

@@ -666,7 +666,7 @@ __global__ void __launch_bounds__(kMaxTile) fwd_tile_kernel(FwdArgs<Real> a) {
 // SIMD, for launches of many tiles (many_tiles); the 64-problem sweep's rates
 // in both builds stand at the batch kernel.  The budget spills 0-132 B per
 // lane.
-template <int N, typename Real, bool COMP, bool CF = false>
+template <int N, typename Real, bool COMP, bool CF>
 __global__ void __launch_bounds__(kMaxTile) __attribute__((amdgpu_waves_per_eu(7, 8)))
 fwd_tile_kernel_many(FwdArgs<Real> a) {
   block_tile<N, Real, ROUTE_ROT, COMP, CF>(a, blockIdx.x);

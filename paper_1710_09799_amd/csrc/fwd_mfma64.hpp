@@ -77,11 +77,17 @@ __device__ __forceinline__ double rows_sum(double x) {
 
 constexpr int kMaxMfma64Tile = 256;  // cells per tile
 
-// C groups of 16 cells per wavefront; blockDim.x = 4 W / C.  CF: E, H and the
+// C groups of 16 cells per wavefront: one leaves a tile of 256 cells 128
+// registers, which spill, four a single wavefront per SIMD (six-level FP64, 50000
+// cells, tiles of 256: 4.2 us per step, 9.4 with one, 4.8 with four).
+constexpr int kMfma64Groups = 2;
+
+// blockDim.x = 4 W / C.  CF: E, H and the
 // source are float-float pairs, carried in FP64 between the ends of a launch
 // and rounded to a pair in every step.
-template <int N, typename Real, bool COMP, bool CF, int C>
-__global__ void __launch_bounds__(4 * kMaxMfma64Tile / C) fwd_mfma64_kernel(FwdArgs<Real> a) {
+template <int N, typename Real, bool COMP, bool CF>
+__global__ void __launch_bounds__(4 * kMaxMfma64Tile / kMfma64Groups) fwd_mfma64_kernel(FwdArgs<Real> a) {
+  constexpr int C = kMfma64Groups;
   using SL = Slots64<N>;
   typedef typename CellType<Real, CF>::type Fld;
   constexpr int D = SL::D, Q = SL::Q, NP = SL::NP, S = SL::S, T = SL::T, R = SL::R;
@@ -454,15 +460,12 @@ __global__ void __launch_bounds__(4 * kMaxMfma64Tile / C) fwd_mfma64_kernel(FwdA
   }
 }
 
-// W: cells per tile, 64, 128, 192 or 256.  Two groups per wavefront: one
-// leaves a tile of 256 cells 128 registers, which spill, four a single
-// wavefront per SIMD (six-level FP64, 50000 cells, tiles of 256: 4.2 us per
-// step, 9.4 with one, 4.8 with four).
+// W: cells per tile, 64, 128, 192 or 256.
 template <int N, typename Real, bool COMP, bool CF>
 hipError_t launch_mfma64(int W, const FwdArgs<Real> &a, int64_t nblocks, hipStream_t st) {
   if (W < 64 || W > kMaxMfma64Tile || W % 64 || a.owned + 2 * a.halo > W || a.tape) return hipErrorInvalidValue;
-  constexpr int C = 2;
-  hipLaunchKernelGGL((fwd_mfma64_kernel<N, Real, COMP, CF, C>), dim3((unsigned)nblocks), dim3(4 * W / C), 0, st, a);
+  hipLaunchKernelGGL((fwd_mfma64_kernel<N, Real, COMP, CF>), dim3((unsigned)nblocks), dim3(4 * W / kMfma64Groups), 0, st,
+                     a);
   return hipGetLastError();
 }
 

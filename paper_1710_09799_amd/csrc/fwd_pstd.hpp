@@ -38,7 +38,7 @@
 // and LDS address, and the medium step of N = 3 keeps its factor in registers
 // (cells.hpp), two of a thread's cells at a time where both are medium.
 // Measured, us per step, half of the ring medium, before / now: N = 3, 1024
-// cells 5.0 / 3.8, 2048 cells 7.2 / 5.2, 4096 cells 13.2 / 10.0; N = 2, 2048
+// cells 5.1 / 4.0, 2048 cells 7.2 / 5.2, 4096 cells 13.1 / 10.3; N = 2, 2048
 // cells 5.0 / 4.0 (its three state components are served well enough by the
 // factor in LDS: 4.2 with cells.hpp).  With eight or more cells per thread
 // pairs of cells would spill (12.2 at 4096 cells).
@@ -341,7 +341,7 @@ __global__ void __launch_bounds__(TMAX) __attribute__((amdgpu_waves_per_eu(pstd_
 fwd_pstd_kernel(PstdArgs a) {
   constexpr int D = N * N - 1;
   constexpr int R = (C + 3) / 4;  // mode pairs per thread: (M / 2) / T rounded up
-  // the medium step of N = 2, 3: cells.hpp, the factor in registers
+  // the medium step of N = 3: cells.hpp, the factor in registers
   constexpr bool CELLS = N == 3;
   // pairs of cells take the short series only, and one by one any other angle:
   // less code in the step (a 2048-cell ring 11.46 ms a run against 11.83 with
