@@ -374,7 +374,7 @@ int mln_grad(mln_handle *h, const double *dJ_dprobe, mln_grads *out);
  * multiple of 16 in [16, 128].  tile 0: 256 (variant 1) or 128;
  * steps_per_launch 0: tile/4; the halo is steps_per_launch cells on each side,
  * so 2 steps_per_launch < tile.  steps_per_launch is an upper bound, as in
- * mln_options (here the boundary cell must not be the first beyond a tile).  The
+ * mln_options: here the boundary cell must not be the first beyond a tile.  The
  * tape is read by cell, so the reverse tiling is independent of the forward
  * one; every tiling gives the same gradient to rounding.  Errors:
  * MLN_EINVAL, MLN_ENOTSUPPORTED (route or N the adjoint does not cover). */
