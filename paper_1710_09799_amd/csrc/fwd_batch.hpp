@@ -48,9 +48,9 @@ __global__ void __launch_bounds__(1024)
 // Float-float fields, compiled for seven wavefronts per SIMD: the default
 // register budget held 3-4 (115 to 135 VGPRs) and left the vector units half
 // idle.  Measured on the 64-problem sweep (tile 256, 16 steps per launch),
-// cell-updates/s against the default budget: compensated state and fields
-// 8.50e10 / 6.61e10, compensated fields 1.46e11 / 1.29e11; five, six and eight
-// wavefronts were slower than seven.  The budget costs spills (12-156 B per
+// cell-updates/s against the default budget, when built: compensated state and
+// fields 8.50e10 / 6.61e10, compensated fields 1.46e11 / 1.29e11; five, six and
+// eight wavefronts were slower than seven.  Since then 9.7e10 and 1.58e11.  The budget costs spills (12-156 B per
 // lane, some inside the step loop); the added wavefronts more than pay for
 // them when there are many tiles (many_tiles).
 template <typename Real, bool COMP, bool CF>
@@ -74,8 +74,8 @@ __global__ void __launch_bounds__(kMaxTile) __attribute__((amdgpu_waves_per_eu(7
 // One wavefront per tile of 64 C cells (fwd_lane.hpp), plain and compensated
 // state.  The 64-problem sweep, tile 256 and 16 steps per launch,
 // cell-updates/s against one cell per thread in its build for seven
-// wavefronts per SIMD: FP64 1.39e11 / 1.01e11, compensated state 1.35e11 /
-// 9.24e10, FP32 1.77e11 / 1.62e11.
+// wavefronts per SIMD: FP64 1.63e11 / 1.01e11, compensated state 1.37e11 /
+// 9.24e10, FP32 2.13e11 / 1.62e11.
 template <typename Real, bool COMP, int C>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(lane_waves<3, Real, COMP, C>(), 8)))
 fwd_lane_batch_kernel(const BatchInst<Real> *__restrict__ inst, const BatchTile *__restrict__ tiles, int64_t step0,

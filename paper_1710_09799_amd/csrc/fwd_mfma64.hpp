@@ -25,11 +25,10 @@
 // v_mfma_f64_16x16x4 takes 64.6 clocks of a SIMD, and every v_fma_f64 beside it
 // adds its 4.1), so the step is bound by arithmetic: N = 6, 1311 clocks of
 // products and about 450 of rotations and fields per 16 cells, 3.0 us for the
-// 256 cells of a compute unit; measured 3.7.  us per step of whole runs with
+// 256 cells of a compute unit; measured 3.9.  us per step of whole runs with
 // the automatic shapes, one cell per thread / this kernel: six levels, 50000
-// cells, FP64 11.4 / 4.3, compensated FP32 15.2 / 4.4; 2000 cells, FP64 9.3 /
-// 2.3; four levels, FP64, 2000 cells 10.2 / 1.9, 50000 10.3 / 2.3, 200000 19.9
-// / 6.1.
+// cells, FP64 11.4 / 4.2, compensated FP32 15.2 / 4.5; 2000 cells, FP64 9.3 /
+// 2.4; four levels, FP64, 2000 cells 10.2 / 1.2, 50000 10.3 / 1.8.
 #pragma once
 
 #include "fwd_lane.hpp"

@@ -21,7 +21,7 @@
 //
 // Measured, three-level beam of 2048 x 512 cells, us per step, one step per
 // launch with a cell per thread / this kernel with the shape the host takes:
-// FP64 27.1 / 15.6, FP32 15.6 / 10.0, compensated FP32 25.0 / 17.8.  The
+// FP64 27.1 / 16.3, FP32 15.6 / 9.7, compensated FP32 25.0 / 18.4.  The
 // workgroup's registers leave one or two of them per compute unit, so its loads
 // (a third of the launch) are not hidden behind another's arithmetic.
 #pragma once
